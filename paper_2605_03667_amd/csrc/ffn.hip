@@ -7,6 +7,7 @@
 
 #include "gemm.h"
 #include "internal.h"
+#include "resident.h"
 
 namespace elas {
 
@@ -32,8 +33,8 @@ struct Carver {
 
 // Transposing job: out[j][i] = in[i][j] for i < rows, j < cols; 0 elsewhere
 // in [out_rows x out_cols].  Copying job (transpose = 0): out[i][j] = in[i][j],
-// 0 elsewhere.  The output is row-major with pitch ldo, or blocked
-// (blocked_index) when nsk > 0.
+// 0 elsewhere.  The output is row-major with pitch ldo, blocked (blocked_index)
+// when nsk > 0, or in fragment order (frag_index) when kp > 0.
 struct TransposeJob {
   const uint16_t* in;
   uint16_t* out;
@@ -42,13 +43,15 @@ struct TransposeJob {
   int tile_begin;   // first flat tile index of this job
   int transpose;
   int64_t nsk;
+  int64_t kp;       // K panels of the fragment order
 };
 __device__ __forceinline__ int64_t job_pos(const TransposeJob& jb, int64_t row, int64_t col) {
+  if (jb.kp > 0) return frag_index(row, col, jb.kp);
   return jb.nsk > 0 ? blocked_index(row, col, jb.nsk) : row * jb.ldo + col;
 }
 // Up to four transposes in one launch (the weight factors of one call): the
 // flat tile index selects the job, so small factors share the launch.
-constexpr int kMaxTransposeJobs = 4;
+constexpr int kMaxTransposeJobs = 5;
 struct TransposeBatch {
   TransposeJob job[kMaxTransposeJobs];
   int n;
@@ -110,9 +113,9 @@ struct Transposes {
   TransposeBatch tb{};
   int tiles = 0;
   void add(const uint16_t* in, int64_t rows, int64_t cols, int64_t ldi, uint16_t* out, int64_t out_rows,
-           int64_t out_cols, int64_t ldo, int transpose = 1, int64_t nsk = 0) {
+           int64_t out_cols, int64_t ldo, int transpose = 1, int64_t nsk = 0, int64_t kp = 0) {
     TransposeJob& j = tb.job[tb.n++];
-    j = TransposeJob{in, out, rows, cols, ldi, out_rows, out_cols, ldo, (int)cdiv(out_cols, 64), tiles, transpose, nsk};
+    j = TransposeJob{in, out, rows, cols, ldi, out_rows, out_cols, ldo, (int)cdiv(out_cols, 64), tiles, transpose, nsk, kp};
     tiles += j.tiles_x * (int)cdiv(out_rows, 64);
   }
   hipError_t launch(hipStream_t st) {
@@ -420,6 +423,54 @@ hipError_t launch_act(const char* tag, const GemmArgs& g, hipStream_t st) {
   return launch<CfgNT<256, EPI, true, 2>>(tag, g, 1, st);
 }
 
+// Token-resident products (resident.h), for the ranks its LDS block is built
+// for.  Whether the d_ff-wide ones (up projection and dH) of T tokens take it:
+// measured faster at every token count (microseconds, tiled kernel against this
+// one: 60M at 512 tokens k2 10.0 / 8.6, b3 11.6 / 9.5; 1B at 2048 29.5 / 21.3,
+// 33.5 / 22.3; 1B at 65536 424 / 307, 478 / 340), except that factors given as A
+// and B would first have to be laid out, a launch of 6 to 10 us that a short
+// forward does not win back.
+bool resident_rank(int64_t r) { return r == 128 || r == 256 || r == 512; }
+bool resident_up(int64_t T, int64_t r, bool ab) { return resident_rank(r) && T > 0 && (!ab || T > 2048); }
+// The d-wide ones (Y and dx), whose few features leave a split-K or 128-wide
+// tiling ahead up to 2048 tokens (1B, k4: 12.6 / 18.4 at 2048, 21.5 / 18.9 at
+// 3000, 149 / 137 at 65536; 60M 7.5 / 8.1, 7.8 / 8.4 and 24.3 / 21.0).
+bool resident_down(int64_t T, int64_t r) { return resident_rank(r) && T > 2048; }
+// Workgroups per block of 128 tokens: the split of the nfb 64-feature blocks
+// with the fewest rounds of wave tiles (copying the tokens costs about 0.4 of
+// one).
+int resident_split(int64_t tiles, int64_t nfb, int64_t r) {
+  const int64_t nw = r == 512 ? 8 : 4, slots = device_cus() * (int64_t)(r == 512 ? 1 : 2);
+  int best = 1;
+  double best_cost = 1e30;
+  for (int64_t s = 1; s <= nfb && s <= 16; ++s) {
+    const double cost = (double)cdiv(tiles * s, slots) * (0.4 + (double)cdiv(cdiv(nfb, s), nw));
+    if (cost < best_cost * 0.98) { best_cost = cost; best = (int)s; }
+  }
+  return best;
+}
+template <int EPI>
+hipError_t launch_resident(const char* tag, int64_t r, ResArgs g, hipStream_t st) {
+  const int64_t tiles = cdiv(g.T, 128);
+  g.fsplit = resident_split(tiles, g.nfb, r);
+  TimedLaunch tl(tag, st);
+  const dim3 grid((unsigned)(tiles * g.fsplit));
+  if (r == 128)
+    hipLaunchKernelGGL((resident_kernel<EPI, 2>), grid, dim3(256), 0, st, g);
+  else if (r == 256)
+    hipLaunchKernelGGL((resident_kernel<EPI, 4>), grid, dim3(256), 0, st, g);
+  else
+    hipLaunchKernelGGL((resident_kernel<EPI, 8>), grid, dim3(512), 0, st, g);
+  return hipGetLastError();
+}
+// C [T x M] = X W^T with W [M x r] in fragment order.
+hipError_t resident_bf16(const char* tag, const uint16_t* W, const uint16_t* X, int64_t T, int64_t M, int64_t r, uint16_t* C,
+                         hipStream_t st) {
+  ResArgs g{};
+  g.W = W; g.X = X; g.ldx = r; g.T = T; g.nfb = (int)(pad64(M) / 64); g.C = C; g.ldc = M; g.f_valid = (int)M;
+  return launch_resident<EPI_BF16>(tag, r, g, st);
+}
+
 // Dense product C[M x N] = A[M x K] * Bt[N x K]^T in bf16 (`part`: split-K
 // partials for small problems, may be null).
 // b_nsk > 0: Bt is blocked (blocked_index, b_nsk K blocks per panel; ldb is
@@ -551,10 +602,11 @@ FwdWs fwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool ab) {
   FwdWs w{};
   if (!ab) {
     w.U_upT = c.take<uint16_t>(r * d);
-    w.V_upT = c.take<uint16_t>(Fp * r);
     w.U_downT = c.take<uint16_t>(r * Fp);
-    w.V_downT = c.take<uint16_t>(d * r);
   }
+  // (fragment order for the token-resident products, also from A and B)
+  if (!ab || resident_up(T, r, ab)) w.V_upT = c.take<uint16_t>(Fp * r);
+  if (!ab || resident_down(T, r)) w.V_downT = c.take<uint16_t>(pad64(d) * r);
   size_t pb = small_split_bytes(T, r, d, 64);                 // k1
   pb = std::max(pb, small_split_bytes(T, r, Fp, 64));          // k3 (2:4 or dense)
   pb = std::max(pb, small_split_bytes(T, d, r, 64));           // k4
@@ -565,6 +617,7 @@ FwdWs fwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool ab) {
 
 struct BwdWs {
   uint16_t *dZ, *dH, *dP, *V_upT;
+  uint16_t *U_downR, *U_upR;   // U_down and U_up in fragment order (token-resident products)
   uint16_t *V_upB, *V_downB;   // V_up [r x F] and V_down [r x d] blocked (the B operands of b5, b1)
   float* part;
   size_t bytes;
@@ -582,6 +635,8 @@ BwdWs bwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bo
   if (ste) w.V_upT = c.take<uint16_t>(Fp * r);
   w.V_upB = c.take<uint16_t>(pad256(r) * Fp);
   w.V_downB = c.take<uint16_t>(pad256(r) * pad64(d));
+  if (!ste && resident_up(T, r, false)) w.U_downR = c.take<uint16_t>(Fp * r);
+  if (resident_down(T, r)) w.U_upR = c.take<uint16_t>(pad64(d) * r);
   // split-K partials of the products over tokens (d_ff-wide ones have Fp rows
   // when read compressed, F rows when dense)
   size_t pb = partial_bytes(r, d, T, false);
@@ -645,17 +700,30 @@ hipError_t run_fwd(const FfnArgs& a, hipStream_t st) {
   // the loads read as zero, exactly like the zero padding of the copies).
   const uint16_t *U_upT = a.U_up, *V_upT = a.V_up, *U_downT = a.U_down, *V_downT = a.V_down;
   int64_t F_rows = F, ld_ud = F;   // rows of V_up^T, pitch (= K extent) of U_down^T
+  // The token-resident products take V_up^T and V_down^T in fragment order, laid
+  // out here from either orientation.
+  const bool res_up = resident_up(T, r, a.ab) && a.fused != 1, res_down = resident_down(T, r) && a.fused != 1;
+  const int64_t kp_up = res_up ? r / 64 : 0, kp_down = res_down ? r / 64 : 0;
+  Transposes tr;
   if (!a.ab) {
-    Transposes tr;
-    tr.add(a.U_up, d, r, r, w.U_upT, r, d, d);          // [r x d]
-    tr.add(a.V_up, r, F, F, w.V_upT, Fp, r, r);         // [Fp x r], zero rows >= F
-    tr.add(a.U_down, F, r, r, w.U_downT, r, Fp, Fp);    // [r x Fp], zero cols >= F
-    tr.add(a.V_down, r, d, d, w.V_downT, d, r, r);      // [d x r]
-    ELAS_TRY(tr.launch(st));
+    tr.add(a.U_up, d, r, r, w.U_upT, r, d, d);                                    // [r x d]
+    tr.add(a.V_up, r, F, F, w.V_upT, Fp, r, r, 1, 0, kp_up);                      // [Fp x r], zero rows >= F
+    tr.add(a.U_down, F, r, r, w.U_downT, r, Fp, Fp);                              // [r x Fp], zero cols >= F
+    tr.add(a.V_down, r, d, d, w.V_downT, res_down ? pad64(d) : d, r, r, 1, 0, kp_down);   // [d x r]
     U_upT = w.U_upT; V_upT = w.V_upT; U_downT = w.U_downT; V_downT = w.V_downT;
     F_rows = Fp;
     ld_ud = Fp;
+  } else {
+    if (res_up) {
+      tr.add(a.V_up, F, r, r, w.V_upT, Fp, r, r, 0, 0, kp_up);
+      V_upT = w.V_upT;
+    }
+    if (res_down) {
+      tr.add(a.V_down, d, r, r, w.V_downT, pad64(d), r, r, 0, 0, kp_down);
+      V_downT = w.V_downT;
+    }
   }
+  ELAS_TRY(tr.launch(st));
   // The one-launch forward only on request: measured slower than the four
   // kernels below at every supported shape but one.
   if (!a.dense && a.fused == 1)
@@ -665,11 +733,18 @@ hipError_t run_fwd(const FfnArgs& a, hipStream_t st) {
   ELAS_TRY(gemm_nt_bf16("k1_up_gemm", a.x, d, U_upT, d, a.P, r, T, r, d, st, w.part));
   if (!a.dense) {
     // H^T = V_up^T P^T with ReLU^2 + 2:4 selection + compression in the epilogue
-    GemmArgs g{};
-    g.A = V_upT; g.lda = r; g.B = a.P; g.ldb = r;
-    g.M = Fp; g.N = T; g.K = r; g.m_valid = F_rows; g.ka_valid = r; g.kb_valid = r;
-    g.sv = a.s_vals; g.sm = a.s_meta; g.ldv = vals_ld(F); g.ldm = meta_ld(F); g.tok = T;   // S written tiled
-    ELAS_TRY(launch_staged<EPI_SPARSIFY>("k2_up_relu2_sparsify", g, st));
+    if (res_up) {
+      ResArgs q{};
+      q.W = V_upT; q.X = a.P; q.ldx = r; q.T = T; q.nfb = (int)(Fp / 64);
+      q.sv = a.s_vals; q.sm = a.s_meta; q.ldv = vals_ld(F); q.ldm = meta_ld(F);
+      ELAS_TRY(launch_resident<EPI_SPARSIFY>("k2_up_relu2_sparsify", r, q, st));
+    } else {
+      GemmArgs g{};
+      g.A = V_upT; g.lda = r; g.B = a.P; g.ldb = r;
+      g.M = Fp; g.N = T; g.K = r; g.m_valid = F_rows; g.ka_valid = r; g.kb_valid = r;
+      g.sv = a.s_vals; g.sm = a.s_meta; g.ldv = vals_ld(F); g.ldm = meta_ld(F); g.tok = T;   // S written tiled
+      ELAS_TRY(launch_staged<EPI_SPARSIFY>("k2_up_relu2_sparsify", g, st));
+    }
     // Z = S U_down on the 2:4 operand
     GemmArgs z{};
     z.A = a.s_vals; z.lda = vals_ld(F); z.Am = a.s_meta; z.ldam = meta_ld(F); z.a_tiled = 1; z.tok = T;
@@ -679,14 +754,21 @@ hipError_t run_fwd(const FfnArgs& a, hipStream_t st) {
     ELAS_TRY(launch_sp("k3_spmm_down", z, st, w.part));
   } else {
     // dense activations: S = relu(H)^2 written [T x F], then a dense product
-    GemmArgs g{};
-    g.A = V_upT; g.lda = r; g.B = a.P; g.ldb = r;
-    g.M = Fp; g.N = T; g.K = r; g.m_valid = F_rows; g.ka_valid = r; g.kb_valid = r;
-    g.act = a.s_vals; g.ld_act = F; g.f_valid = F; g.act_square = 1;
-    ELAS_TRY(launch_act<EPI_ACT_DENSE>("k2_up_relu2_dense", g, st));
+    if (res_up) {
+      ResArgs q{};
+      q.W = V_upT; q.X = a.P; q.ldx = r; q.T = T; q.nfb = (int)(Fp / 64); q.C = a.s_vals; q.ldc = F; q.f_valid = (int)F;
+      ELAS_TRY(launch_resident<EPI_ACT_DENSE>("k2_up_relu2_dense", r, q, st));
+    } else {
+      GemmArgs g{};
+      g.A = V_upT; g.lda = r; g.B = a.P; g.ldb = r;
+      g.M = Fp; g.N = T; g.K = r; g.m_valid = F_rows; g.ka_valid = r; g.kb_valid = r;
+      g.act = a.s_vals; g.ld_act = F; g.f_valid = F; g.act_square = 1;
+      ELAS_TRY(launch_act<EPI_ACT_DENSE>("k2_up_relu2_dense", g, st));
+    }
     ELAS_TRY(gemm_nt_bf16("k3_down_gemm_dense", a.s_vals, F, U_downT, ld_ud, a.Z, r, T, r, F, st, w.part));
   }
   // Y = Z V_down
+  if (res_down) return resident_bf16("k4_down_gemm", V_downT, a.Z, T, d, r, a.y, st);
   ELAS_TRY(gemm_nt_bf16("k4_down_gemm", a.Z, r, V_downT, r, a.y, d, T, d, r, st, w.part));
   return hipSuccess;
 }
@@ -726,12 +808,15 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
   // cache lines.  Both are copied blocked (one contiguous 32 KB block per
   // tile K step: measured 7 % faster for dP at 1B), and V_up^T for the
   // straight-through backward, in one launch.
+  const bool res_up = resident_up(T, r, false), res_down = resident_down(T, r);
   const int64_t nsk_vu = Fp / 64, nsk_vd = pad64(d) / 64;
   {
     Transposes tr;
     tr.add(a.V_up, r, F, F, w.V_upB, pad256(r), Fp, 0, 0, nsk_vu);
     tr.add(a.V_down, r, d, d, w.V_downB, pad256(r), pad64(d), 0, 0, nsk_vd);
     if (a.ste) tr.add(a.V_up, r, F, F, w.V_upT, Fp, r, r);      // [Fp x r], zero rows >= F
+    if (res_up && !a.ste) tr.add(a.U_down, F, r, r, w.U_downR, Fp, r, r, 0, 0, r / 64);
+    if (res_down) tr.add(a.U_up, d, r, r, w.U_upR, pad64(d), r, r, 0, 0, r / 64);
     ELAS_TRY(tr.launch(st));
   }
   // dZ = dY V_down^T
@@ -740,11 +825,18 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
   ELAS_TRY(gemm_tt_f32<OP_T>("b2_dV_down", a.Z, r, nullptr, 0, a.dy, d, r, d, T, w.part, a.dV_down, r, false, d, st));
   if (!a.dense && !a.ste) {
     // dH = (dZ U_down^T) * mask * 2 relu(H), computed as dS^T = U_down dZ^T
-    GemmArgs g{};
-    g.A = a.U_down; g.lda = r; g.B = w.dZ; g.ldb = r;
-    g.M = Fp; g.N = T; g.K = r; g.m_valid = F; g.ka_valid = r; g.kb_valid = r;
-    g.sv = a.s_vals; g.sm = a.s_meta; g.ldv = ldv; g.ldm = ldm; g.dv = w.dH; g.tok = T;   // S read, dH written, tiled
-    ELAS_TRY(launch_staged<EPI_DH>("b3_dH_masked", g, st));
+    if (res_up) {
+      ResArgs q{};
+      q.W = w.U_downR; q.X = w.dZ; q.ldx = r; q.T = T; q.nfb = (int)(Fp / 64);
+      q.sv = a.s_vals; q.sm = a.s_meta; q.ldv = ldv; q.ldm = ldm; q.dv = w.dH;
+      ELAS_TRY(launch_resident<EPI_DH>("b3_dH_masked", r, q, st));
+    } else {
+      GemmArgs g{};
+      g.A = a.U_down; g.lda = r; g.B = w.dZ; g.ldb = r;
+      g.M = Fp; g.N = T; g.K = r; g.m_valid = F; g.ka_valid = r; g.kb_valid = r;
+      g.sv = a.s_vals; g.sm = a.s_meta; g.ldv = ldv; g.ldm = ldm; g.dv = w.dH; g.tok = T;   // S read, dH written, tiled
+      ELAS_TRY(launch_staged<EPI_DH>("b3_dH_masked", g, st));
+    }
     // dU_down = S^T dZ from the compressed S
     ELAS_TRY(gemm_tt_f32<OP_TSP>("b4_dU_down", a.s_vals, ldv, a.s_meta, ldm, w.dZ, r, Fp, r, T, w.part, a.dU_down, F,
                                  false, r, st));
@@ -772,6 +864,11 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
       // dS^T = U_down dZ^T over the next r
       g.A = w.V_upT; g.B = a.P_in; g.A2 = a.U_down; g.B2 = w.dZ;
       ELAS_TRY(launch_act<EPI_DH_STE>("b3_dH_ste", g, st));
+    } else if (res_up) {
+      ResArgs q{};
+      q.W = w.U_downR; q.X = w.dZ; q.ldx = r; q.T = T; q.nfb = (int)(Fp / 64);
+      q.C = w.dH; q.act = a.s_vals; q.ldc = F; q.f_valid = (int)F;
+      ELAS_TRY(launch_resident<EPI_DH_DENSE>("b3_dH_dense", r, q, st));
     } else {
       g.act = const_cast<uint16_t*>(a.s_vals); g.act_square = 1;
       ELAS_TRY(launch_act<EPI_DH_DENSE>("b3_dH_dense", g, st));
@@ -793,6 +890,7 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
   // dU_up = x^T dP
   ELAS_TRY(gemm_tt_f32<OP_T>("b7_dU_up", a.x, d, nullptr, 0, w.dP, r, d, r, T, w.part, a.dU_up, d, false, r, st));
   // dx = dP U_up^T   (U_up [d x r] is already K-contiguous)
+  if (res_down) return resident_bf16("b8_dx", w.U_upR, w.dP, T, d, r, a.dx, st);
   ELAS_TRY(gemm_nt_bf16("b8_dx", w.dP, r, a.U_up, r, a.dx, d, T, d, r, st, w.part));
   return hipSuccess;
 }

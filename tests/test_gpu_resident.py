@@ -1,0 +1,34 @@
+"""The token-resident products at the edges of their blocks: token counts
+around 128 and 2048 (where the products to the model width change kernel), d
+and d_ff that are not multiples of 64, each rank, each activation mode, against
+the oracle with the gates of the other parity tests."""
+import pytest
+import torch
+
+import paper_2605_03667_amd as elas
+from oracle import ffn as offn
+from synthetic import ffn_inputs
+from tests.helpers import dev_bf16
+from tests.test_gpu_ffn import compare, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("mode", ["sparse", "dense"])
+@pytest.mark.parametrize("T,d,F,r", [(1, 64, 64, 128), (127, 72, 72, 256), (129, 200, 1000, 512), (2049, 136, 328, 128),
+                                     (2303, 72, 200, 256), (2431, 520, 456, 512)])
+def test_resident_edges(T, d, F, r, mode):
+    bits = ffn_inputs(T, d, F, r, seed_base=T + r)
+    f, b = offn.run(bits, sparse=(mode != "dense"))
+    compare(run_gpu(bits, mode=mode), f, b, bits, mode=mode)
+
+
+@pytest.mark.parametrize("T,d,F,r", [(2049, 136, 328, 128), (2431, 520, 456, 512)])
+def test_resident_factors_ab_identical(T, d, F, r):
+    """Factors given as A and B are laid out by another job of the same launch."""
+    t = {k: dev_bf16(v) for k, v in ffn_inputs(T, d, F, r, seed_base=5).items()}
+    w = [t[k] for k in ("U_up", "V_up", "U_down", "V_down")]
+    a = elas.elas_lowrank_ffn_fwd(t["x"], *w)
+    b = elas.elas_lowrank_ffn_fwd(t["x"], *[x.t().contiguous() for x in w], flags=elas.ELAS_FACTORS_AB)
+    for k in a:
+        assert torch.equal(a[k], b[k]), k
