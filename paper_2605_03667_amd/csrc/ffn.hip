@@ -8,6 +8,7 @@
 #include "gemm.h"
 #include "internal.h"
 #include "resident.h"
+#include "small.h"
 
 namespace elas {
 
@@ -423,15 +424,15 @@ hipError_t launch_act(const char* tag, const GemmArgs& g, hipStream_t st) {
   return launch<CfgNT<256, EPI, true, 2>>(tag, g, 1, st);
 }
 
-// Token-resident products (resident.h), for the ranks its LDS block is built
-// for.  Whether the d_ff-wide ones (up projection and dH) of T tokens take it:
-// measured faster at every token count (microseconds, tiled kernel against this
-// one: 60M at 512 tokens k2 10.0 / 8.6, b3 11.6 / 9.5; 1B at 2048 29.5 / 21.3,
-// 33.5 / 22.3; 1B at 65536 424 / 307, 478 / 340), except that factors given as A
-// and B would first have to be laid out, a launch of 6 to 10 us that a short
-// forward does not win back.
+// Token-resident products (resident.h), for the ranks its LDS block is built for.
 bool resident_rank(int64_t r) { return r == 128 || r == 256 || r == 512; }
-bool resident_up(int64_t T, int64_t r, bool ab) { return resident_rank(r) && T > 0 && (!ab || T > 2048); }
+// The d_ff-wide ones (up projection and dH) are faster than the tiled kernel at
+// every token count (microseconds, tiled against this: 60M at 512 tokens k2
+// 10.0 / 8.6, b3 11.6 / 9.5; 1B at 2048 29.5 / 21.3, 33.5 / 22.3; 1B at 65536
+// 424 / 307, 478 / 340), but where nothing else is laid out in the call, laying
+// the weights out in fragment order is a launch of its own (6 to 10 us), which up
+// to 2048 tokens costs more than it gives.
+bool resident_wide(int64_t T, int64_t r, bool laid_out) { return resident_rank(r) && T > 0 && (laid_out || T > 2048); }
 // The d-wide ones (Y and dx), whose few features leave a split-K or 128-wide
 // tiling ahead up to 2048 tokens (1B, k4: 12.6 / 18.4 at 2048, 21.5 / 18.9 at
 // 3000, 149 / 137 at 65536; 60M 7.5 / 8.1, 7.8 / 8.4 and 24.3 / 21.0).
@@ -469,6 +470,94 @@ hipError_t resident_bf16(const char* tag, const uint16_t* W, const uint16_t* X, 
   ResArgs g{};
   g.W = W; g.X = X; g.ldx = r; g.T = T; g.nfb = (int)(pad64(M) / 64); g.C = C; g.ldc = M; g.f_valid = (int)M;
   return launch_resident<EPI_BF16>(tag, r, g, st);
+}
+
+// Wave-split products (small.h).
+template <int EPI, bool SP, int TT, int FI, int KS, int FW, int D>
+hipError_t launch_small_as(const char* tag, SmallArgs g, hipStream_t st) {
+  if (KS > 1 && g.chunk == 0) g.chunk = (int)cdiv(cdiv(g.K, 64), KS);
+  if (KS == 1) g.chunk = (int)cdiv(g.K, 64);
+  TimedLaunch tl(tag, st);
+  const dim3 grid((unsigned)cdiv(g.M, FW * FI * 16), (unsigned)cdiv(g.T, TT * 16));
+  hipLaunchKernelGGL((small_kernel<EPI, SP, TT, FI, KS, FW, D>), grid, dim3(64 * KS * FW), 0, st, g);
+  return hipGetLastError();
+}
+// Long contractions (over d or d_ff) to M features: K over 16 waves of a
+// workgroup with 16 features of 16 or 32 tokens, or over 8 with 32 features of
+// 64.  Taken as long as each CU has at most one workgroup; a second one per CU
+// doubles the time, and the tiled kernel wins (us, the tiled kernel and its reduce
+// against this one: k1 at 1B, 16 tokens 14.5 + 6.7 / 7.8, 256 12.0 + 6.2 / 9.8,
+// 1024 12.5 + 6.3 / 15.4; 350M at 2000 tokens 15.0 + 6.2 / 10.6; k3 at 1B, 16 tokens
+// 18.9 + 6.5 / 9.6, 256 13.9 + 6.2 / 12.8, 1024 15.7 + 6.3 / 20.5).
+int small_long_shape(int64_t T, int64_t M) {
+  const int64_t cus = device_cus();
+  if (T <= 0) return 0;
+  if (cdiv(M, 16) * cdiv(T, 32) <= cus) return T <= 16 ? 1 : 2;
+  return cdiv(M, 32) * cdiv(T, 64) <= cus ? 3 : 0;
+}
+template <bool SP>
+hipError_t launch_small_long(const char* tag, const SmallArgs& g, hipStream_t st) {
+  switch (small_long_shape(g.T, g.M)) {
+    case 1: return launch_small_as<EPI_BF16, SP, 1, 1, 16, 1, 3>(tag, g, st);
+    case 2: return launch_small_as<EPI_BF16, SP, 2, 1, 16, 1, 3>(tag, g, st);
+    default: return launch_small_as<EPI_BF16, SP, 4, 2, 8, 1, 2>(tag, g, st);
+  }
+}
+// P = x U_up: a rounding of P decides what the selection ranks, so K is cut as
+// the tiled kernel's split-K cuts it (into 1, 2 or 4 chunks here) and P is the
+// same bits.
+template <int KS>
+hipError_t launch_small_k1_as(SmallArgs g, hipStream_t st) {
+  if (small_long_shape(g.T, g.M) == 1) return launch_small_as<EPI_BF16, false, 1, 1, KS, 1, 8>("k1_up_gemm", g, st);
+  if (small_long_shape(g.T, g.M) == 2) return launch_small_as<EPI_BF16, false, 2, 1, KS, 1, 4>("k1_up_gemm", g, st);
+  return launch_small_as<EPI_BF16, false, 4, 2, KS, 1, 2>("k1_up_gemm", g, st);
+}
+hipError_t launch_small_k1(SmallArgs g, const SmallSplit& p, hipStream_t st) {
+  g.chunk = (int)(p.k_split / 64);
+  if (p.splits == 1) return launch_small_k1_as<1>(g, st);
+  return p.splits == 2 ? launch_small_k1_as<2>(g, st) : launch_small_k1_as<4>(g, st);
+}
+// Short ones (over r): features over the waves, each with the whole of K (the
+// tiled kernel's order of sums), by the same measure (k2 at 1B, 64 tokens 19.0 /
+// 10.6; k4 at 1B, 256 tokens 11.4 / 9.9; k4 at 350M, 500 tokens 10.4 / 7.3).
+bool small_short(int64_t T, int64_t M) { return T > 0 && cdiv(M, 64) * cdiv(T, 32) <= device_cus(); }
+template <int EPI>
+hipError_t launch_small_short(const char* tag, const SmallArgs& g, hipStream_t st) {
+  if (g.T <= 16) return launch_small_as<EPI, false, 1, 1, 1, 4, 8>(tag, g, st);
+  return launch_small_as<EPI, false, 2, 1, 1, 4, 4>(tag, g, st);
+}
+// C [T x M] = X W^T, W [M x K].
+SmallArgs small_dense(const uint16_t* W, int64_t ldw, int64_t M, int64_t K, const uint16_t* X, int64_t ldx, int64_t T, uint16_t* C) {
+  SmallArgs g{};
+  g.W = W; g.ldw = ldw; g.m_valid = g.M = (int)M; g.kw_valid = g.K = (int)K;
+  g.X = X; g.ldx = ldx; g.T = T; g.C = C; g.ldc = M;
+  return g;
+}
+// C [T x M] = S W^T with S compressed (tiled) along K = F features, W [M x ldw].
+SmallArgs small_sp(const uint16_t* W, int64_t ldw, int64_t M, int64_t F, const uint16_t* sv, const uint8_t* sm, int64_t T, uint16_t* C) {
+  SmallArgs g{};
+  g.W = W; g.ldw = ldw; g.m_valid = g.M = (int)M; g.kw_valid = (int)F; g.K = (int)pad64(F);
+  g.X = sv; g.Xm = sm; g.ldx = vals_ld(F); g.ldxm = meta_ld(F); g.T = T; g.C = C; g.ldc = M;
+  return g;
+}
+// The kernel of each product of one call.
+enum Route { TILED, SMALL, RESIDENT };
+// Z, dZ and dP; P.
+Route route_long(int64_t T, int64_t M) { return small_long_shape(T, M) ? SMALL : TILED; }
+Route route_k1(int64_t T, int64_t d, int64_t r) {
+  const int n = plan_small_split(T, r, d, 64).splits;
+  return small_long_shape(T, r) && few_tiles(T, r, 256, r <= 128 ? 128 : 256) && (n <= 2 || n == 4) ? SMALL : TILED;
+}
+// The up projection and masked dH (sparse mode) or their dense counterparts;
+// laid_out: the call lays out weights anyway.
+Route route_wide(int64_t T, int64_t F, int64_t r, bool dense, bool laid_out) {
+  if (!dense && small_short(T, pad64(F))) return SMALL;
+  return resident_wide(T, r, laid_out) ? RESIDENT : TILED;
+}
+// Y and dx.
+Route route_down(int64_t T, int64_t d, int64_t r) {
+  if (small_short(T, d)) return SMALL;
+  return resident_down(T, r) ? RESIDENT : TILED;
 }
 
 // Dense product C[M x N] = A[M x K] * Bt[N x K]^T in bf16 (`part`: split-K
@@ -596,7 +685,7 @@ struct FwdWs {
   size_t bytes;
 };
 // (ab: the caller passes the factors already K-contiguous; no copies)
-FwdWs fwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool ab) {
+FwdWs fwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ab) {
   const int64_t Fp = pad64(F);
   Carver c{p};
   FwdWs w{};
@@ -605,8 +694,8 @@ FwdWs fwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool ab) {
     w.U_downT = c.take<uint16_t>(r * Fp);
   }
   // (fragment order for the token-resident products, also from A and B)
-  if (!ab || resident_up(T, r, ab)) w.V_upT = c.take<uint16_t>(Fp * r);
-  if (!ab || resident_down(T, r)) w.V_downT = c.take<uint16_t>(pad64(d) * r);
+  if (!ab || route_wide(T, F, r, dense, !ab) == RESIDENT) w.V_upT = c.take<uint16_t>(Fp * r);
+  if (!ab || route_down(T, d, r) == RESIDENT) w.V_downT = c.take<uint16_t>(pad64(d) * r);
   size_t pb = small_split_bytes(T, r, d, 64);                 // k1
   pb = std::max(pb, small_split_bytes(T, r, Fp, 64));          // k3 (2:4 or dense)
   pb = std::max(pb, small_split_bytes(T, d, r, 64));           // k4
@@ -635,8 +724,8 @@ BwdWs bwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bo
   if (ste) w.V_upT = c.take<uint16_t>(Fp * r);
   w.V_upB = c.take<uint16_t>(pad256(r) * Fp);
   w.V_downB = c.take<uint16_t>(pad256(r) * pad64(d));
-  if (!ste && resident_up(T, r, false)) w.U_downR = c.take<uint16_t>(Fp * r);
-  if (resident_down(T, r)) w.U_upR = c.take<uint16_t>(pad64(d) * r);
+  if (!ste && route_wide(T, F, r, dense, route_long(T, r) == TILED) == RESIDENT) w.U_downR = c.take<uint16_t>(Fp * r);
+  if (route_down(T, d, r) == RESIDENT) w.U_upR = c.take<uint16_t>(pad64(d) * r);
   // split-K partials of the products over tokens (d_ff-wide ones have Fp rows
   // when read compressed, F rows when dense)
   size_t pb = partial_bytes(r, d, T, false);
@@ -666,8 +755,7 @@ size_t spmm_workspace_bytes(int64_t K, int64_t N, int b_layout) {
 }
 
 size_t fwd_workspace_bytes(int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ab) {
-  (void)dense;
-  return fwd_ws(nullptr, T, d, F, r, ab).bytes;
+  return fwd_ws(nullptr, T, d, F, r, dense, ab).bytes;
 }
 
 size_t bwd_workspace_bytes(int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ste) {
@@ -694,31 +782,31 @@ hipError_t run_spmm24(const uint16_t* a_vals, const uint8_t* a_meta, int64_t M, 
 
 hipError_t run_fwd(const FfnArgs& a, hipStream_t st) {
   const int64_t T = a.T, d = a.d, F = a.F, r = a.r, Fp = pad64(F);
-  const FwdWs w = fwd_ws((char*)a.ws, T, d, F, r, a.ab);
+  const FwdWs w = fwd_ws((char*)a.ws, T, d, F, r, a.dense, a.ab);
   // Weight factors K-contiguous for the MFMA operands: laid out here, or
   // given so (ELAS_FACTORS_AB: unpadded d_ff, whose missing rows / columns
   // the loads read as zero, exactly like the zero padding of the copies).
   const uint16_t *U_upT = a.U_up, *V_upT = a.V_up, *U_downT = a.U_down, *V_downT = a.V_down;
   int64_t F_rows = F, ld_ud = F;   // rows of V_up^T, pitch (= K extent) of U_down^T
-  // The token-resident products take V_up^T and V_down^T in fragment order, laid
-  // out here from either orientation.
-  const bool res_up = resident_up(T, r, a.ab) && a.fused != 1, res_down = resident_down(T, r) && a.fused != 1;
-  const int64_t kp_up = res_up ? r / 64 : 0, kp_down = res_down ? r / 64 : 0;
+  const bool fused = !a.dense && a.fused == 1;
+  const Route up = fused ? TILED : route_wide(T, F, r, a.dense, !a.ab), down = fused ? TILED : route_down(T, d, r);
+  // The token-resident products take V_up^T and V_down^T in fragment order.
+  const int64_t kp_up = up == RESIDENT ? r / 64 : 0, kp_down = down == RESIDENT ? r / 64 : 0;
   Transposes tr;
   if (!a.ab) {
     tr.add(a.U_up, d, r, r, w.U_upT, r, d, d);                                    // [r x d]
     tr.add(a.V_up, r, F, F, w.V_upT, Fp, r, r, 1, 0, kp_up);                      // [Fp x r], zero rows >= F
     tr.add(a.U_down, F, r, r, w.U_downT, r, Fp, Fp);                              // [r x Fp], zero cols >= F
-    tr.add(a.V_down, r, d, d, w.V_downT, res_down ? pad64(d) : d, r, r, 1, 0, kp_down);   // [d x r]
+    tr.add(a.V_down, r, d, d, w.V_downT, kp_down ? pad64(d) : d, r, r, 1, 0, kp_down);   // [d x r]
     U_upT = w.U_upT; V_upT = w.V_upT; U_downT = w.U_downT; V_downT = w.V_downT;
     F_rows = Fp;
     ld_ud = Fp;
   } else {
-    if (res_up) {
+    if (kp_up) {
       tr.add(a.V_up, F, r, r, w.V_upT, Fp, r, r, 0, 0, kp_up);
       V_upT = w.V_upT;
     }
-    if (res_down) {
+    if (kp_down) {
       tr.add(a.V_down, d, r, r, w.V_downT, pad64(d), r, r, 0, 0, kp_down);
       V_downT = w.V_downT;
     }
@@ -726,49 +814,66 @@ hipError_t run_fwd(const FfnArgs& a, hipStream_t st) {
   ELAS_TRY(tr.launch(st));
   // The one-launch forward only on request: measured slower than the four
   // kernels below at every supported shape but one.
-  if (!a.dense && a.fused == 1)
+  if (fused)
     return run_fused_fwd(a.x, U_upT, V_upT, U_downT, V_downT, T, d, F, r, F_rows, ld_ud, a.y, a.P, a.s_vals,
                          a.s_meta, a.Z, st);
   // P = x U_up
-  ELAS_TRY(gemm_nt_bf16("k1_up_gemm", a.x, d, U_upT, d, a.P, r, T, r, d, st, w.part));
+  if (route_k1(T, d, r) == SMALL)
+    ELAS_TRY(launch_small_k1(small_dense(U_upT, d, r, d, a.x, d, T, a.P), plan_small_split(T, r, d, 64), st));
+  else
+    ELAS_TRY(gemm_nt_bf16("k1_up_gemm", a.x, d, U_upT, d, a.P, r, T, r, d, st, w.part));
+  ResArgs q{};   // the up projection
+  q.W = V_upT; q.X = a.P; q.ldx = r; q.T = T; q.nfb = (int)(Fp / 64);
   if (!a.dense) {
     // H^T = V_up^T P^T with ReLU^2 + 2:4 selection + compression in the epilogue
-    if (res_up) {
-      ResArgs q{};
-      q.W = V_upT; q.X = a.P; q.ldx = r; q.T = T; q.nfb = (int)(Fp / 64);
-      q.sv = a.s_vals; q.sm = a.s_meta; q.ldv = vals_ld(F); q.ldm = meta_ld(F);
-      ELAS_TRY(launch_resident<EPI_SPARSIFY>("k2_up_relu2_sparsify", r, q, st));
+    const char* tag = "k2_up_relu2_sparsify";
+    q.sv = a.s_vals; q.sm = a.s_meta; q.ldv = vals_ld(F); q.ldm = meta_ld(F);
+    if (up == SMALL) {
+      SmallArgs g = small_dense(V_upT, r, F, r, a.P, r, T, nullptr);
+      g.M = (int)Fp;
+      g.sv = a.s_vals; g.sm = a.s_meta; g.ldv = vals_ld(F); g.ldm = meta_ld(F);
+      ELAS_TRY(launch_small_short<EPI_SPARSIFY>(tag, g, st));
+    } else if (up == RESIDENT) {
+      ELAS_TRY(launch_resident<EPI_SPARSIFY>(tag, r, q, st));
     } else {
       GemmArgs g{};
       g.A = V_upT; g.lda = r; g.B = a.P; g.ldb = r;
       g.M = Fp; g.N = T; g.K = r; g.m_valid = F_rows; g.ka_valid = r; g.kb_valid = r;
       g.sv = a.s_vals; g.sm = a.s_meta; g.ldv = vals_ld(F); g.ldm = meta_ld(F); g.tok = T;   // S written tiled
-      ELAS_TRY(launch_staged<EPI_SPARSIFY>("k2_up_relu2_sparsify", g, st));
+      ELAS_TRY(launch_staged<EPI_SPARSIFY>(tag, g, st));
     }
     // Z = S U_down on the 2:4 operand
-    GemmArgs z{};
-    z.A = a.s_vals; z.lda = vals_ld(F); z.Am = a.s_meta; z.ldam = meta_ld(F); z.a_tiled = 1; z.tok = T;
-    z.B = U_downT; z.ldb = ld_ud;
-    z.M = T; z.N = r; z.K = Fp; z.m_valid = T; z.ka_valid = Fp; z.kb_valid = ld_ud;
-    z.C = a.Z; z.ldc = r;
-    ELAS_TRY(launch_sp("k3_spmm_down", z, st, w.part));
+    if (route_long(T, r) == SMALL) {
+      ELAS_TRY(launch_small_long<true>("k3_spmm_down", small_sp(U_downT, ld_ud, r, F, a.s_vals, a.s_meta, T, a.Z), st));
+    } else {
+      GemmArgs z{};
+      z.A = a.s_vals; z.lda = vals_ld(F); z.Am = a.s_meta; z.ldam = meta_ld(F); z.a_tiled = 1; z.tok = T;
+      z.B = U_downT; z.ldb = ld_ud;
+      z.M = T; z.N = r; z.K = Fp; z.m_valid = T; z.ka_valid = Fp; z.kb_valid = ld_ud;
+      z.C = a.Z; z.ldc = r;
+      ELAS_TRY(launch_sp("k3_spmm_down", z, st, w.part));
+    }
   } else {
     // dense activations: S = relu(H)^2 written [T x F], then a dense product
-    if (res_up) {
-      ResArgs q{};
-      q.W = V_upT; q.X = a.P; q.ldx = r; q.T = T; q.nfb = (int)(Fp / 64); q.C = a.s_vals; q.ldc = F; q.f_valid = (int)F;
-      ELAS_TRY(launch_resident<EPI_ACT_DENSE>("k2_up_relu2_dense", r, q, st));
+    const char* tag = "k2_up_relu2_dense";
+    q.C = a.s_vals; q.ldc = F; q.f_valid = (int)F;
+    if (up == RESIDENT) {
+      ELAS_TRY(launch_resident<EPI_ACT_DENSE>(tag, r, q, st));
     } else {
       GemmArgs g{};
       g.A = V_upT; g.lda = r; g.B = a.P; g.ldb = r;
       g.M = Fp; g.N = T; g.K = r; g.m_valid = F_rows; g.ka_valid = r; g.kb_valid = r;
       g.act = a.s_vals; g.ld_act = F; g.f_valid = F; g.act_square = 1;
-      ELAS_TRY(launch_act<EPI_ACT_DENSE>("k2_up_relu2_dense", g, st));
+      ELAS_TRY(launch_act<EPI_ACT_DENSE>(tag, g, st));
     }
-    ELAS_TRY(gemm_nt_bf16("k3_down_gemm_dense", a.s_vals, F, U_downT, ld_ud, a.Z, r, T, r, F, st, w.part));
+    if (route_long(T, r) == SMALL)
+      ELAS_TRY(launch_small_long<false>("k3_down_gemm_dense", small_dense(U_downT, ld_ud, r, F, a.s_vals, F, T, a.Z), st));
+    else
+      ELAS_TRY(gemm_nt_bf16("k3_down_gemm_dense", a.s_vals, F, U_downT, ld_ud, a.Z, r, T, r, F, st, w.part));
   }
   // Y = Z V_down
-  if (res_down) return resident_bf16("k4_down_gemm", V_downT, a.Z, T, d, r, a.y, st);
+  if (down == SMALL) return launch_small_short<EPI_BF16>("k4_down_gemm", small_dense(V_downT, r, d, r, a.Z, r, T, a.y), st);
+  if (down == RESIDENT) return resident_bf16("k4_down_gemm", V_downT, a.Z, T, d, r, a.y, st);
   ELAS_TRY(gemm_nt_bf16("k4_down_gemm", a.Z, r, V_downT, r, a.y, d, T, d, r, st, w.part));
   return hipSuccess;
 }
@@ -808,45 +913,61 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
   // cache lines.  Both are copied blocked (one contiguous 32 KB block per
   // tile K step: measured 7 % faster for dP at 1B), and V_up^T for the
   // straight-through backward, in one launch.
-  const bool res_up = resident_up(T, r, false), res_down = resident_down(T, r);
+  const Route lng = route_long(T, r), down = route_down(T, d, r);
+  const Route wide = a.ste ? TILED : route_wide(T, F, r, a.dense, lng == TILED);
   const int64_t nsk_vu = Fp / 64, nsk_vd = pad64(d) / 64;
   {
     Transposes tr;
-    tr.add(a.V_up, r, F, F, w.V_upB, pad256(r), Fp, 0, 0, nsk_vu);
-    tr.add(a.V_down, r, d, d, w.V_downB, pad256(r), pad64(d), 0, 0, nsk_vd);
+    if (lng == TILED) {
+      tr.add(a.V_up, r, F, F, w.V_upB, pad256(r), Fp, 0, 0, nsk_vu);
+      tr.add(a.V_down, r, d, d, w.V_downB, pad256(r), pad64(d), 0, 0, nsk_vd);
+    }
     if (a.ste) tr.add(a.V_up, r, F, F, w.V_upT, Fp, r, r);      // [Fp x r], zero rows >= F
-    if (res_up && !a.ste) tr.add(a.U_down, F, r, r, w.U_downR, Fp, r, r, 0, 0, r / 64);
-    if (res_down) tr.add(a.U_up, d, r, r, w.U_upR, pad64(d), r, r, 0, 0, r / 64);
+    if (wide == RESIDENT) tr.add(a.U_down, F, r, r, w.U_downR, Fp, r, r, 0, 0, r / 64);
+    if (down == RESIDENT) tr.add(a.U_up, d, r, r, w.U_upR, pad64(d), r, r, 0, 0, r / 64);
     ELAS_TRY(tr.launch(st));
   }
   // dZ = dY V_down^T
-  ELAS_TRY(gemm_nt_bf16("b1_dZ", a.dy, d, w.V_downB, d, w.dZ, r, T, r, d, st, w.part, nsk_vd));
+  if (lng == SMALL)
+    ELAS_TRY(launch_small_long<false>("b1_dZ", small_dense(a.V_down, d, r, d, a.dy, d, T, w.dZ), st));
+  else
+    ELAS_TRY(gemm_nt_bf16("b1_dZ", a.dy, d, w.V_downB, d, w.dZ, r, T, r, d, st, w.part, nsk_vd));
   // dV_down = Z^T dY
   ELAS_TRY(gemm_tt_f32<OP_T>("b2_dV_down", a.Z, r, nullptr, 0, a.dy, d, r, d, T, w.part, a.dV_down, r, false, d, st));
+  ResArgs q{};   // dS = dZ U_down^T
+  q.W = w.U_downR; q.X = w.dZ; q.ldx = r; q.T = T; q.nfb = (int)(Fp / 64);
   if (!a.dense && !a.ste) {
     // dH = (dZ U_down^T) * mask * 2 relu(H), computed as dS^T = U_down dZ^T
-    if (res_up) {
-      ResArgs q{};
-      q.W = w.U_downR; q.X = w.dZ; q.ldx = r; q.T = T; q.nfb = (int)(Fp / 64);
-      q.sv = a.s_vals; q.sm = a.s_meta; q.ldv = ldv; q.ldm = ldm; q.dv = w.dH;
-      ELAS_TRY(launch_resident<EPI_DH>("b3_dH_masked", r, q, st));
+    const char* tag = "b3_dH_masked";
+    q.sv = a.s_vals; q.sm = a.s_meta; q.ldv = ldv; q.ldm = ldm; q.dv = w.dH;
+    if (wide == SMALL) {
+      SmallArgs g = small_dense(a.U_down, r, F, r, w.dZ, r, T, nullptr);
+      g.M = (int)Fp;
+      g.sv = a.s_vals; g.sm = a.s_meta; g.ldv = ldv; g.ldm = ldm; g.dv = w.dH;
+      ELAS_TRY(launch_small_short<EPI_DH>(tag, g, st));
+    } else if (wide == RESIDENT) {
+      ELAS_TRY(launch_resident<EPI_DH>(tag, r, q, st));
     } else {
       GemmArgs g{};
       g.A = a.U_down; g.lda = r; g.B = w.dZ; g.ldb = r;
       g.M = Fp; g.N = T; g.K = r; g.m_valid = F; g.ka_valid = r; g.kb_valid = r;
       g.sv = a.s_vals; g.sm = a.s_meta; g.ldv = ldv; g.ldm = ldm; g.dv = w.dH; g.tok = T;   // S read, dH written, tiled
-      ELAS_TRY(launch_staged<EPI_DH>("b3_dH_masked", g, st));
+      ELAS_TRY(launch_staged<EPI_DH>(tag, g, st));
     }
     // dU_down = S^T dZ from the compressed S
     ELAS_TRY(gemm_tt_f32<OP_TSP>("b4_dU_down", a.s_vals, ldv, a.s_meta, ldm, w.dZ, r, Fp, r, T, w.part, a.dU_down, F,
                                  false, r, st));
-    // dP = dH V_up^T on the 2:4 operand (V_up blocked)
-    GemmArgs p{};
-    p.A = w.dH; p.lda = ldv; p.Am = a.s_meta; p.ldam = ldm; p.a_tiled = 1; p.tok = T;
-    p.B = w.V_upB; p.ldb = 64; p.b_nsk = nsk_vu;
-    p.M = T; p.N = r; p.K = Fp; p.m_valid = T; p.ka_valid = Fp; p.kb_valid = F;
-    p.C = w.dP; p.ldc = r;
-    ELAS_TRY(launch_sp("b5_spmm_dP", p, st, w.part));
+    // dP = dH V_up^T on the 2:4 operand (tiled kernel: V_up blocked)
+    if (lng == SMALL) {
+      ELAS_TRY(launch_small_long<true>("b5_spmm_dP", small_sp(a.V_up, F, r, F, w.dH, a.s_meta, T, w.dP), st));
+    } else {
+      GemmArgs p{};
+      p.A = w.dH; p.lda = ldv; p.Am = a.s_meta; p.ldam = ldm; p.a_tiled = 1; p.tok = T;
+      p.B = w.V_upB; p.ldb = 64; p.b_nsk = nsk_vu;
+      p.M = T; p.N = r; p.K = Fp; p.m_valid = T; p.ka_valid = Fp; p.kb_valid = F;
+      p.C = w.dP; p.ldc = r;
+      ELAS_TRY(launch_sp("b5_spmm_dP", p, st, w.part));
+    }
     // dV_up = P^T dH, computed as dV_up^T = dH^T P and written transposed
     ELAS_TRY(gemm_tt_f32<OP_TSP>("b6_dV_up", w.dH, ldv, a.s_meta, ldm, a.P_in, r, Fp, r, T, w.part, a.dV_up, F, true, F,
                                  st));
@@ -864,9 +985,7 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
       // dS^T = U_down dZ^T over the next r
       g.A = w.V_upT; g.B = a.P_in; g.A2 = a.U_down; g.B2 = w.dZ;
       ELAS_TRY(launch_act<EPI_DH_STE>("b3_dH_ste", g, st));
-    } else if (res_up) {
-      ResArgs q{};
-      q.W = w.U_downR; q.X = w.dZ; q.ldx = r; q.T = T; q.nfb = (int)(Fp / 64);
+    } else if (wide == RESIDENT) {
       q.C = w.dH; q.act = a.s_vals; q.ldc = F; q.f_valid = (int)F;
       ELAS_TRY(launch_resident<EPI_DH_DENSE>("b3_dH_dense", r, q, st));
     } else {
@@ -882,7 +1001,10 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
                                    F, false, r, st));
     }
     // dP = dH V_up^T (dense)
-    ELAS_TRY(gemm_nt_bf16("b5_dP_dense", w.dH, F, w.V_upB, F, w.dP, r, T, r, F, st, w.part, nsk_vu));
+    if (lng == SMALL)
+      ELAS_TRY(launch_small_long<false>("b5_dP_dense", small_dense(a.V_up, F, r, F, w.dH, F, T, w.dP), st));
+    else
+      ELAS_TRY(gemm_nt_bf16("b5_dP_dense", w.dH, F, w.V_upB, F, w.dP, r, T, r, F, st, w.part, nsk_vu));
     // dV_up^T = dH^T P (dense), written transposed
     ELAS_TRY(gemm_tt_f32<OP_T>("b6_dV_up_dense", w.dH, F, nullptr, 0, a.P_in, r, F, r, T, w.part, a.dV_up, F, true,
                                F, st));
@@ -890,7 +1012,8 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
   // dU_up = x^T dP
   ELAS_TRY(gemm_tt_f32<OP_T>("b7_dU_up", a.x, d, nullptr, 0, w.dP, r, d, r, T, w.part, a.dU_up, d, false, r, st));
   // dx = dP U_up^T   (U_up [d x r] is already K-contiguous)
-  if (res_down) return resident_bf16("b8_dx", w.U_upR, w.dP, T, d, r, a.dx, st);
+  if (down == SMALL) return launch_small_short<EPI_BF16>("b8_dx", small_dense(a.U_up, r, d, r, w.dP, r, T, a.dx), st);
+  if (down == RESIDENT) return resident_bf16("b8_dx", w.U_upR, w.dP, T, d, r, a.dx, st);
   ELAS_TRY(gemm_nt_bf16("b8_dx", w.dP, r, a.U_up, r, a.dx, d, T, d, r, st, w.part));
   return hipSuccess;
 }

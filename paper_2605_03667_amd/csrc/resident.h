@@ -43,7 +43,7 @@ typedef __attribute__((address_space(1))) u32x4 gu32x4;
 typedef __attribute__((address_space(1))) u32x2 gu32x2;
 
 struct ResArgs {
-  const uint16_t* W;   // frag_index layout, nfb blocks of 64 features, kp panels
+  const uint16_t* W;   // frag_index layout, nfb blocks of 64 features
   const uint16_t* X;   // tokens [T x K], pitch ldx
   int64_t ldx, T;
   int nfb;             // blocks of 64 features
@@ -228,7 +228,6 @@ __global__ __launch_bounds__(KP == 8 ? 512 : 256, 2) void resident_kernel(const 
       if (lane == 0) nxt = atomicAdd(&s_next, 1);
       nxt = __builtin_amdgcn_readfirstlane(nxt);
     }
-    const u32x4* wn = block_ptr(nxt < f_end ? nxt : cur);
     if constexpr (READS) {
       copy_codes(cur);
 #pragma unroll
@@ -238,6 +237,7 @@ __global__ __launch_bounds__(KP == 8 ? 512 : 256, 2) void resident_kernel(const 
     panel(std::true_type{}, std::false_type{}, 0, wp + 512);
 #pragma unroll
     for (int q = 1; q + 1 < KP; ++q) panel(std::false_type{}, std::false_type{}, q, wp + (q + 1) * 512);
+    const u32x4* wn = block_ptr(nxt < f_end ? nxt : cur);
     panel(std::false_type{}, std::true_type{}, KP - 1, wn);
     __builtin_amdgcn_s_setprio(1);
     // ---- epilogue: features 64 cur .. + 63.  Element e of acc[i][j] in lane l
