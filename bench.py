@@ -48,6 +48,13 @@ PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 
 
+# The weight gradients share one launch; its work is that of its four products.
+GROUPED = {
+    "b2467_weight_grads": ("b2_dV_down", "b4_dU_down", "b6_dV_up", "b7_dU_up"),
+    "b2467_weight_grads_ste": ("b2_dV_down", "b4_dU_down", "b6_dV_up_dense", "b7_dU_up"),
+}
+
+
 def algorithmic_flops(tag: str, T: int, d: int, F: int, r: int) -> float | None:
     """Algorithmic FLOP of one launch of a kernel tag (T tokens per launch).
 
@@ -55,6 +62,8 @@ def algorithmic_flops(tag: str, T: int, d: int, F: int, r: int) -> float | None:
     the 2:4 activation count only the kept half (T r F instead of 2 T r F),
     including the masked dH product whose discarded half is still computed.
     """
+    if tag in GROUPED:
+        return sum(algorithmic_flops(t, T, d, F, r) for t in GROUPED[tag])
     table = {
         "k1_up_gemm": 2 * T * d * r, "k2_up_relu2_sparsify": 2 * T * r * F, "k3_spmm_down": T * r * F,
         "k4_down_gemm": 2 * T * r * d, "b1_dZ": 2 * T * d * r, "b2_dV_down": 2 * T * d * r,
@@ -69,6 +78,8 @@ def algorithmic_flops(tag: str, T: int, d: int, F: int, r: int) -> float | None:
 
 def executed_flops(tag: str, T: int, d: int, F: int, r: int) -> float | None:
     """FLOP the kernel actually issues (dense-equivalent for smfmac)."""
+    if tag in GROUPED:
+        return sum(executed_flops(t, T, d, F, r) for t in GROUPED[tag])
     a = algorithmic_flops(tag, T, d, F, r)
     if a is None:
         return None
@@ -88,6 +99,8 @@ def algorithmic_bytes(tag: str, T: int, d: int, F: int, r: int) -> float | None:
     activation 1.125 B per feature (kept values plus 2-bit codes, Table 2's
     storage), its metadata 0.125 B per feature when read with dH's values,
     fp32 weight gradients 4 B per element."""
+    if tag in GROUPED:
+        return sum(algorithmic_bytes(t, T, d, F, r) for t in GROUPED[tag])
     S = T * F * 1.125                 # compressed S: F/2 bf16 values + F/8 code bytes per token
     dH = T * F * 1.0                  # compressed dH values (its codes are S's)
     meta = T * F * 0.125

@@ -9,6 +9,7 @@
 #include "internal.h"
 #include "resident.h"
 #include "small.h"
+#include "wgrad.h"
 
 namespace elas {
 
@@ -134,86 +135,6 @@ hipError_t transpose_pad(const uint16_t* in, int64_t rows, int64_t cols, int64_t
   return t.launch(st);
 }
 
-// Writes a 64 x 64 (m, n) tile of sums held as acc[i] = row m0 + ty + 16 i,
-// float4 columns n0 + 4 tx: to out[m][n], or to out[n][m] when transposing
-// (through LDS, so that consecutive threads store consecutive m).  N and a
-// non-transposed ldo are multiples of 4 (the model dimensions are multiples
-// of 8).
-__device__ __forceinline__ void reduce_store(const float4 (&acc)[4], int64_t m0, int64_t n0, int tx, int ty,
-                                             int64_t N, int64_t rows_out, int transpose, float* __restrict__ out,
-                                             int64_t ldo, float (*tile)[65]) {
-  const int64_t n = n0 + 4 * tx;
-  if (!transpose) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t m = m0 + ty + 16 * i;
-      if (m < rows_out && n < N) *(float4*)(out + m * ldo + n) = acc[i];
-    }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    tile[4 * tx + 0][ty + 16 * i] = acc[i].x;
-    tile[4 * tx + 1][ty + 16 * i] = acc[i].y;
-    tile[4 * tx + 2][ty + 16 * i] = acc[i].z;
-    tile[4 * tx + 3][ty + 16 * i] = acc[i].w;
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < 64 * 64; q += 256) {
-    const int r = q / 64, c = q % 64;
-    const int64_t on = n0 + r, om = m0 + c;
-    if (on < N && om < rows_out) out[on * ldo + om] = tile[r][c];
-  }
-}
-
-// out[m][n] (or out[n][m]) = sum over the splits k, in order (so the result
-// is deterministic), of part[k][m][n], for rows m < rows_out; one 64 x 64
-// (m, n) tile per block.
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ part, int splits, int64_t M,
-                                                           int64_t N, int64_t rows_out, int transpose,
-                                                           float* __restrict__ out, int64_t ldo) {
-  __shared__ float tile[64][65];
-  const int64_t m0 = (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  const int64_t n = n0 + 4 * tx;
-  float4 acc[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-  // Splits are read four at a time (16 loads in flight per thread) and added
-  // in split order, so the result does not depend on the grouping.
-  int k = 0;
-  for (; k + 4 <= splits; k += 4) {
-    float4 v[4][4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const float* pk = part + (int64_t)(k + u) * M * N;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int64_t m = m0 + ty + 16 * i;
-        v[u][i] = (m < rows_out && n < N) ? *(const float4*)(pk + m * N + n) : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        acc[i].x += v[u][i].x; acc[i].y += v[u][i].y; acc[i].z += v[u][i].z; acc[i].w += v[u][i].w;
-      }
-  }
-  for (; k < splits; ++k) {
-    const float* pk = part + (int64_t)k * M * N;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t m = m0 + ty + 16 * i;
-      if (m < rows_out && n < N) {
-        const float4 v = *(const float4*)(pk + m * N + n);
-        acc[i].x += v.x; acc[i].y += v.y; acc[i].z += v.z; acc[i].w += v.w;
-      }
-    }
-  }
-  reduce_store(acc, m0, n0, tx, ty, N, rows_out, transpose, out, ldo, tile);
-}
-
 // bf16 result of a split-K product with a bf16 output: out[m][n] =
 // bf16(sum over the splits k, in order, of part[k][m][n]); one 4-column piece
 // per thread (N and ldo are multiples of 8).
@@ -229,54 +150,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_bf16_kernel(const float* __
     acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
   }
   *(uint2*)(out + m * ldo + n) = make_uint2(bf16x2_rne(acc.x, acc.y), bf16x2_rne(acc.z, acc.w));
-}
-
-// The stream-K counterpart: workgroup w of `wgs` owns iterations
-// [w I / wgs, (w+1) I / wgs) of the I = ntiles x S (tile, K step) space and
-// wrote the partial of the j-th tile it touched to part + (w segs + j) 256^2
-// (256 x 256 row-major).  The sums run over the workgroups in order, i.e. in
-// K order, so the result is deterministic.
-__global__ __launch_bounds__(256) void streamk_reduce_kernel(const float* __restrict__ part, int wgs, int segs,
-                                                            int64_t S, int tiles_n, int64_t ntiles, int64_t N,
-                                                            int64_t rows_out, int transpose, float* __restrict__ out,
-                                                            int64_t ldo) {
-  __shared__ float tile[64][65];
-  const int64_t m0 = (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  const int64_t t = (m0 / 256) * tiles_n + n0 / 256;
-  const int lm = (int)(m0 % 256), ln = (int)(n0 % 256) + 4 * tx;
-  const int64_t I = ntiles * S, tb = t * S, te = tb + S;
-  auto beg_of = [&](int64_t w) { return w * I / wgs; };
-  int64_t w = tb * wgs / I;   // the workgroup whose range holds iteration tb
-  while (w > 0 && beg_of(w) > tb) --w;
-  while (beg_of(w + 1) <= tb) ++w;
-  float4 acc[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-  // The workgroups [w, w_end) that touch tile t, read four at a time (16
-  // loads in flight per thread) and added in workgroup order.
-  int64_t w_end = w;
-  while (w_end < wgs && beg_of(w_end) < te) ++w_end;
-  for (; w < w_end; w += 4) {
-    float4 v[4][4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t wu = w + u;
-      const int64_t b = beg_of(wu), e = beg_of(wu + 1);
-      const bool has = wu < w_end && e > b;
-      const float* slot = part + ((int64_t)wu * segs + (t - b / S)) * 65536;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        v[u][i] = has ? *(const float4*)(slot + (int64_t)(lm + ty + 16 * i) * 256 + ln) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        acc[i].x += v[u][i].x; acc[i].y += v[u][i].y; acc[i].z += v[u][i].z; acc[i].w += v[u][i].w;
-      }
-  }
-  reduce_store(acc, m0, n0, tx, ty, N, rows_out, transpose, out, ldo, tile);
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(float* __restrict__ p, int64_t n) {
@@ -307,14 +180,6 @@ using CfgNT3 = CfgNT<256, EPI_BF16, false, 1>;
 // streams from HBM, and the third stage covers more of its latency.
 // (Measured: 22% faster than 256 x 128 tiles with 128-K steps in two stages.)
 using CfgSP = GemmCfg<256, 256, 4, 2, OP_SP, OP_K, EPI_BF16, false, 3, true, false, 64>;
-// Contraction over tokens (K = T): both operands stored [T x rows].
-// Both operands are K-major: the dense ones go to LDS by DMA, the 2:4 one is
-// expanded in registers; fragments are read with the transposing LDS read.
-// K = T weight-gradient products (both operands token-major and streaming;
-// a three-stage ring for one of them measured no gain).
-template <int AMODE>
-using CfgTT = GemmCfg<256, 256, 4, 2, AMODE, OP_T, EPI_F32, false>;
-
 // Compute units of the current device (cached per device id).
 // (Relaxed atomics: concurrent first calls store the same value.)
 int device_cus() {
@@ -342,7 +207,7 @@ hipError_t launch(const char* tag, GemmArgs g, int splits, hipStream_t st) {
   // looping over its tiles.
   const int tiles = g.tiles_m * g.tiles_n;
   const int cus = device_cus();
-  const int wgs = Cfg::DIRECT && tiles > cus ? cus : tiles;
+  const int wgs = tiles > cus ? cus : tiles;
   const dim3 grid((unsigned)wgs, (unsigned)splits);
   TimedLaunch tl(tag, st);
   hipLaunchKernelGGL(gemm_kernel<Cfg>, grid, dim3(Cfg::NT), 0, st, g);
@@ -585,99 +450,67 @@ hipError_t gemm_nt_bf16(const char* tag, const uint16_t* A, int64_t lda, const u
   return launch<CfgNT3>(tag, g, 1, st);
 }
 
-// Work split of a K = T product.  Split-K: enough workgroups to cover the 256
-// CUs once, each split at least 8 K steps long (more splits fill the CUs more
-// evenly but cost more partial-sum traffic than they save at the 1B shapes);
-// below 16 steps (T < 1024) and for outputs under 2^20 elements, splits may be
-// 2 steps long, since there the latency of a few long workgroups dominates
-// (measured: the 60M backward at 512 tokens 134 -> 93 us; the same rule was
-// slower at 2048 tokens and above, and for the 1B shape's larger outputs).
-// When that leaves more than a tenth of the CUs idle, the register-staged
-// (2:4) products use stream-K instead: 256 workgroups with equal shares of
-// the tiles x K steps, each at least 8 steps.
-constexpr int kStreamWgs = 256;
-// Products that even split fill at most half the CUs with 256 x 256 tiles
-// (short K at small token counts) use 128 x 128 tiles and split-K only.
-struct SplitPlan {
-  int splits;
-  int64_t k_split;
-  int64_t stream_steps;   // > 0: stream-K with this many K steps per tile
-  int segs;               // stream-K partial tiles per workgroup
-  bool small;             // 128 x 128 tiles
-};
-SplitPlan plan_tiles(int64_t M, int64_t N, int64_t K, int tb) {
-  const int64_t tiles = cdiv(M, tb) * cdiv(N, tb);
-  const int64_t steps = cdiv(K, 64);
-  const int64_t min_steps = steps < 16 && M * N < (1 << 20) ? 2 : 8;
-  int64_t s = 256 / tiles;
-  if (s < 1) s = 1;
-  if (s > steps / min_steps) s = steps / min_steps > 0 ? steps / min_steps : 1;
-  const int64_t k_split = cdiv(cdiv(K, s), 64) * 64;
-  return {(int)cdiv(K, k_split), k_split, 0, 0, tb == 128};
-}
-SplitPlan plan_splits(int64_t M, int64_t N, int64_t K, bool allow_stream) {
-  if (K <= 0) return {0, 0, 0, 0, false};
-  const SplitPlan big = plan_tiles(M, N, K, 256);
-  const int64_t tiles = cdiv(M, 256) * cdiv(N, 256), steps = cdiv(K, 64);
-  if (tiles * big.splits * 2 <= kStreamWgs) {
-    const SplitPlan sm = plan_tiles(M, N, K, 128);
-    if (cdiv(M, 128) * cdiv(N, 128) * sm.splits > 2 * tiles * big.splits) return sm;
+// Weight gradients (wgrad.h): the jobs of one backward and how their (tile, step)
+// list is shared out.
+struct WgradPlan {
+  WgradArgs g{};
+  int tb = 0, njobs = 0, rblocks = 0;
+  void add(const uint16_t* A, int64_t lda, const uint8_t* Am, int64_t ldam, const uint16_t* B, int64_t M, int64_t N,
+           float* out, int64_t rows_out, bool transpose) {
+    WgradJob& j = g.job[njobs++];
+    j = WgradJob{};
+    j.A = A; j.lda = lda; j.Am = Am; j.ldam = ldam; j.sparse = Am != nullptr;
+    j.B = B; j.ldb = N; j.M = M; j.N = N;
+    j.out = out; j.rows_out = rows_out; j.transpose = transpose; j.ldo = transpose ? rows_out : N;
   }
-  if (allow_stream && tiles * big.splits * 10 < 9LL * kStreamWgs && tiles * steps >= 8LL * kStreamWgs) {
-    const int64_t longest = cdiv(tiles * steps, kStreamWgs);
-    return {1, K, steps, (int)((longest - 1) / steps + 2), false};
+  // 256-wide tiles as long as each of one workgroup per CU gets about 6 steps;
+  // else 128-wide ones, two workgroups per CU, at least 4 steps each (fewer steps
+  // than that cost more in partial tiles than the extra workgroups give).
+  void finish(int64_t T) {
+    const int64_t steps = cdiv(T, 64), cus = device_cus();
+    auto tiles = [&](int b) {
+      int64_t n = 0;
+      for (int k = 0; k < njobs; ++k) n += cdiv(g.job[k].M, b) * cdiv(g.job[k].N, b);
+      return n;
+    };
+    tb = tiles(256) * steps >= 6 * cus ? 256 : 128;
+    int64_t nt = 0;
+    for (int k = 0; k < kWgradJobs; ++k) {
+      WgradJob& j = g.job[k];
+      j.tile0 = (int)nt;
+      j.rblock0 = rblocks;
+      if (k >= njobs) {   // never reached
+        j.tile0 = j.rblock0 = INT32_MAX;
+        continue;
+      }
+      j.tiles_n = (int)cdiv(j.N, tb);
+      j.rblocks_n = (int)cdiv(j.N, 64);
+      nt += cdiv(j.M, tb) * j.tiles_n;
+      rblocks += j.rblocks_n * (int)cdiv(j.rows_out, 64);
+    }
+    const int64_t slots = tb == 256 ? cus : 2 * cus;
+    int64_t c = std::min(slots / nt, tb == 256 ? steps : steps / 4);
+    if (c < 1) c = 1;
+    g.T = T;
+    g.steps = (int)steps;
+    g.ntiles = (int)nt;
+    g.chunks = (int)c;
   }
-  return big;
-}
-size_t partial_bytes(int64_t M, int64_t N, int64_t K, bool allow_stream) {
-  const SplitPlan p = plan_splits(M, N, K, allow_stream);
-  if (p.stream_steps > 0) return (size_t)kStreamWgs * p.segs * 256 * 256 * sizeof(float);
-  return (size_t)p.splits * M * N * sizeof(float);
-}
-
-// C = A^T B summed over K = T rows, reduced into out (optionally transposed),
-// keeping rows m < rows_out.  A is [K x M] dense (OP_T) or 2:4 compressed
-// along M (OP_TSP); B is [K x N] dense.
-template <int AMODE>
-using CfgTTs = GemmCfg<128, 128, 2, 2, AMODE, OP_T, EPI_F32, false>;
-
-template <int AMODE>
-hipError_t gemm_tt_f32(const char* tag, const uint16_t* A, int64_t lda, const uint8_t* Am, int64_t ldam, const uint16_t* B,
-                       int64_t ldb, int64_t M, int64_t N, int64_t K, float* part, float* out, int64_t rows_out,
-                       bool transpose, int64_t ldo, hipStream_t st) {
-  if (K == 0) return hipSuccess;
-  using Cfg = CfgTT<AMODE>;
-  const SplitPlan p = plan_splits(M, N, K, AMODE == OP_TSP);
-  GemmArgs g{};
-  g.A = A; g.lda = lda; g.Am = Am; g.ldam = ldam; g.B = B; g.ldb = ldb;
-  g.M = M; g.N = N; g.K = K; g.m_valid = M; g.ka_valid = K; g.kb_valid = K;
-  g.k_split = p.k_split; g.C = part; g.ldc = N;
-  if (AMODE == OP_TSP) g.tok = K;   // the compressed operand is tiled over its K (token) rows
-  const dim3 rgrid((unsigned)cdiv(N, 64), (unsigned)cdiv(rows_out, 64));
-  if (p.stream_steps > 0) {
-    static_assert(Cfg::BM == 256 && Cfg::BN == 256, "stream-K partial tiles are 256 x 256");
-    g.stream_steps = p.stream_steps;
-    g.stream_segs = p.segs;
-    g.tiles_m = (int)cdiv(M, Cfg::BM);
-    g.tiles_n = (int)cdiv(N, Cfg::BN);
+  size_t part_floats() const { return (size_t)g.ntiles * g.chunks * tb * tb; }
+  hipError_t launch(const char* tag, hipStream_t st) const {
     {
       TimedLaunch tl(tag, st);
-      hipLaunchKernelGGL(gemm_kernel<Cfg>, dim3(kStreamWgs), dim3(Cfg::NT), 0, st, g);
+      if (tb == 256) hipLaunchKernelGGL(wgrad_kernel<256>, dim3((unsigned)(g.ntiles * g.chunks)), dim3(512), 0, st, g);
+      else hipLaunchKernelGGL(wgrad_kernel<128>, dim3((unsigned)(g.ntiles * g.chunks)), dim3(256), 0, st, g);
     }
-    hipError_t e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    TimedLaunch tl("splitk_reduce", st);
-    hipLaunchKernelGGL(streamk_reduce_kernel, rgrid, dim3(256), 0, st, part, kStreamWgs, p.segs, p.stream_steps,
-                       g.tiles_n, (int64_t)g.tiles_m * g.tiles_n, N, rows_out, transpose ? 1 : 0, out, ldo);
+    TimedLaunch tl("wgrad_reduce", st);
+    if (tb == 256) hipLaunchKernelGGL(wgrad_reduce_kernel<256>, dim3((unsigned)rblocks), dim3(256), 0, st, g);
+    else hipLaunchKernelGGL(wgrad_reduce_kernel<128>, dim3((unsigned)rblocks), dim3(256), 0, st, g);
     return hipGetLastError();
   }
-  hipError_t e = p.small ? launch<CfgTTs<AMODE>>(tag, g, p.splits, st) : launch<Cfg>(tag, g, p.splits, st);
-  if (e != hipSuccess) return e;
-  TimedLaunch tl("splitk_reduce", st);
-  hipLaunchKernelGGL(splitk_reduce_kernel, rgrid, dim3(256), 0, st, part, p.splits, M, N, rows_out,
-                     transpose ? 1 : 0, out, ldo);
-  return hipGetLastError();
-}
+};
 
 struct FwdWs {
   uint16_t *U_upT, *V_upT, *U_downT, *V_downT;
@@ -711,6 +544,23 @@ struct BwdWs {
   float* part;
   size_t bytes;
 };
+// dV_down = Z^T dY; dU_down = S^T dZ from the compressed (or dense) S; dV_up =
+// P^T dH as dV_up^T = dH^T P, written transposed; dU_up = x^T dP.
+WgradPlan wgrad_plan(const FfnArgs& a, const BwdWs& w, bool dense, bool ste) {
+  const int64_t T = a.T, d = a.d, F = a.F, r = a.r, Fp = pad64(F), ldv = vals_ld(F), ldm = meta_ld(F);
+  static const uint8_t planning = 0;   // (sizes only: the pointers are not set yet)
+  const uint8_t* sm = a.s_meta ? a.s_meta : &planning;
+  WgradPlan p;
+  p.add(a.Z, r, nullptr, 0, a.dy, r, d, a.dV_down, r, false);
+  if (dense) p.add(a.s_vals, F, nullptr, 0, w.dZ, F, r, a.dU_down, F, false);
+  else p.add(a.s_vals, ldv, sm, ldm, w.dZ, Fp, r, a.dU_down, F, false);
+  if (dense || ste) p.add(w.dH, F, nullptr, 0, a.P_in, F, r, a.dV_up, F, true);
+  else p.add(w.dH, ldv, sm, ldm, a.P_in, Fp, r, a.dV_up, F, true);
+  p.add(a.x, d, nullptr, 0, w.dP, d, r, a.dU_up, d, false);
+  p.finish(T);
+  p.g.part = w.part;
+  return p;
+}
 // dH is compressed [T x ldv] in the sparse backward and dense [T x F] in the
 // dense and straight-through ones; the straight-through backward also holds
 // V_up^T (relu(h) is recomputed tile by tile inside the dH kernel).
@@ -726,14 +576,9 @@ BwdWs bwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bo
   w.V_downB = c.take<uint16_t>(pad256(r) * pad64(d));
   if (!ste && route_wide(T, F, r, dense, route_long(T, r) == TILED) == RESIDENT) w.U_downR = c.take<uint16_t>(Fp * r);
   if (route_down(T, d, r) == RESIDENT) w.U_upR = c.take<uint16_t>(pad64(d) * r);
-  // split-K partials of the products over tokens (d_ff-wide ones have Fp rows
-  // when read compressed, F rows when dense)
-  size_t pb = partial_bytes(r, d, T, false);
-  const size_t p2 = partial_bytes(Fp, r, T, true), p3 = partial_bytes(d, r, T, false), p4 = partial_bytes(F, r, T, false);
-  if (p2 > pb) pb = p2;
-  if (p3 > pb) pb = p3;
-  if (p4 > pb) pb = p4;
-  // split-K of the long-K bf16 products at small token counts (b1, b5, b8)
+  // partials: the weight gradients', and split-K of the long-K bf16 products at
+  // small token counts (b1, b5, b8)
+  size_t pb = T > 0 ? wgrad_plan(FfnArgs{T, d, F, r}, w, dense, ste).part_floats() * sizeof(float) : 0;
   pb = std::max(pb, small_split_bytes(T, r, d, 64));
   pb = std::max(pb, small_split_bytes(T, r, Fp, 64));
   pb = std::max(pb, small_split_bytes(T, d, r, 64));
@@ -932,8 +777,6 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
     ELAS_TRY(launch_small_long<false>("b1_dZ", small_dense(a.V_down, d, r, d, a.dy, d, T, w.dZ), st));
   else
     ELAS_TRY(gemm_nt_bf16("b1_dZ", a.dy, d, w.V_downB, d, w.dZ, r, T, r, d, st, w.part, nsk_vd));
-  // dV_down = Z^T dY
-  ELAS_TRY(gemm_tt_f32<OP_T>("b2_dV_down", a.Z, r, nullptr, 0, a.dy, d, r, d, T, w.part, a.dV_down, r, false, d, st));
   ResArgs q{};   // dS = dZ U_down^T
   q.W = w.U_downR; q.X = w.dZ; q.ldx = r; q.T = T; q.nfb = (int)(Fp / 64);
   if (!a.dense && !a.ste) {
@@ -954,9 +797,6 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
       g.sv = a.s_vals; g.sm = a.s_meta; g.ldv = ldv; g.ldm = ldm; g.dv = w.dH; g.tok = T;   // S read, dH written, tiled
       ELAS_TRY(launch_staged<EPI_DH>(tag, g, st));
     }
-    // dU_down = S^T dZ from the compressed S
-    ELAS_TRY(gemm_tt_f32<OP_TSP>("b4_dU_down", a.s_vals, ldv, a.s_meta, ldm, w.dZ, r, Fp, r, T, w.part, a.dU_down, F,
-                                 false, r, st));
     // dP = dH V_up^T on the 2:4 operand (tiled kernel: V_up blocked)
     if (lng == SMALL) {
       ELAS_TRY(launch_small_long<true>("b5_spmm_dP", small_sp(a.V_up, F, r, F, w.dH, a.s_meta, T, w.dP), st));
@@ -968,9 +808,6 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
       p.C = w.dP; p.ldc = r;
       ELAS_TRY(launch_sp("b5_spmm_dP", p, st, w.part));
     }
-    // dV_up = P^T dH, computed as dV_up^T = dH^T P and written transposed
-    ELAS_TRY(gemm_tt_f32<OP_TSP>("b6_dV_up", w.dH, ldv, a.s_meta, ldm, a.P_in, r, Fp, r, T, w.part, a.dV_up, F, true, F,
-                                 st));
   } else {
     // dense dH [T x F] = dS * 2 r at every position: r = bf16(sqrt(s)) from the
     // dense S (dense mode), or relu(h) recomputed from P and V_up (straight-
@@ -992,25 +829,15 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
       g.act = const_cast<uint16_t*>(a.s_vals); g.act_square = 1;
       ELAS_TRY(launch_act<EPI_DH_DENSE>("b3_dH_dense", g, st));
     }
-    if (a.dense) {
-      // dU_down = S^T dZ with the dense S
-      ELAS_TRY(gemm_tt_f32<OP_T>("b4_dU_down_dense", a.s_vals, F, nullptr, 0, w.dZ, r, F, r, T, w.part, a.dU_down, F,
-                                 false, r, st));
-    } else {
-      ELAS_TRY(gemm_tt_f32<OP_TSP>("b4_dU_down", a.s_vals, ldv, a.s_meta, ldm, w.dZ, r, Fp, r, T, w.part, a.dU_down,
-                                   F, false, r, st));
-    }
     // dP = dH V_up^T (dense)
     if (lng == SMALL)
       ELAS_TRY(launch_small_long<false>("b5_dP_dense", small_dense(a.V_up, F, r, F, w.dH, F, T, w.dP), st));
     else
       ELAS_TRY(gemm_nt_bf16("b5_dP_dense", w.dH, F, w.V_upB, F, w.dP, r, T, r, F, st, w.part, nsk_vu));
-    // dV_up^T = dH^T P (dense), written transposed
-    ELAS_TRY(gemm_tt_f32<OP_T>("b6_dV_up_dense", w.dH, F, nullptr, 0, a.P_in, r, F, r, T, w.part, a.dV_up, F, true,
-                               F, st));
   }
-  // dU_up = x^T dP
-  ELAS_TRY(gemm_tt_f32<OP_T>("b7_dU_up", a.x, d, nullptr, 0, w.dP, r, d, r, T, w.part, a.dU_up, d, false, r, st));
+  // the four weight gradients
+  ELAS_TRY(wgrad_plan(a, w, a.dense, a.ste).launch(a.dense ? "b2467_weight_grads_dense" : a.ste ? "b2467_weight_grads_ste"
+                                                                                             : "b2467_weight_grads", st));
   // dx = dP U_up^T   (U_up [d x r] is already K-contiguous)
   if (down == SMALL) return launch_small_short<EPI_BF16>("b8_dx", small_dense(a.U_up, r, d, r, w.dP, r, T, a.dx), st);
   if (down == RESIDENT) return resident_bf16("b8_dx", w.U_upR, w.dP, T, d, r, a.dx, st);

@@ -14,22 +14,12 @@
 // buffers: the loads of step s + STAGES - 1 are issued while step s computes,
 // and each wave waits only for its own loads of step s (an exact vmcnt)
 // before a plain s_barrier.  Lanes whose chunk lies outside the matrix load
-// from a zero block.  K-contiguous operands land in K-contiguous LDS rows;
-// K-major operands ([K x rows] in memory) land K-major and their MFMA
-// fragments are read with the transposing ds_read_b64_tr_b16.  The 2:4
-// operand read along its rows (S^T, dH^T) is expanded in registers and
-// written K-major after the current step's MFMAs.  One barrier per step.
+// from a zero block.  One barrier per step.
 //
 // Operand modes:
 //   OP_K    operand stored [rows x K] row-major (K contiguous): 16-byte copies.
-//   OP_T    operand stored [K x rows] (rows contiguous): DMA to a K-major LDS
-//           tile, fragments by transposing LDS reads.
 //   OP_SP   (A only) 2:4 compressed along K: kept values [rows x K/2] plus
 //           metadata [rows x K/8]; consumed by v_smfmac_f32_32x32x32_bf16.
-//   OP_TSP  (A only) 2:4 compressed along the row dimension of a [K x rows]
-//           matrix (S^T or dH^T read from the compressed activation): each
-//           thread expands 16 features of one contraction row from kept values
-//           + metadata into the K-major LDS tile.
 //
 // MFMA layouts (pinned on gfx950 by a probe against a CPU product):
 //   v_mfma_f32_32x32x16_bf16: lane l holds A[row l%32][k 8(l/32)..+8] and
@@ -52,7 +42,7 @@
 namespace elas {
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
-enum OpMode { OP_K = 0, OP_T = 1, OP_SP = 2, OP_TSP = 3 };
+enum OpMode { OP_K = 0, OP_SP = 2 };
 enum EpiMode {
   EPI_BF16 = 0,       // C bf16
   EPI_F32 = 1,        // fp32 split-K partials
@@ -64,11 +54,11 @@ enum EpiMode {
 };
 
 struct GemmArgs {
-  const uint16_t* A;   // OP_K [M x K], OP_T [K x M], OP_SP vals [M x K/2], OP_TSP vals [K x M/2]
+  const uint16_t* A;   // OP_K [M x K], OP_SP vals [M x K/2]
   int64_t lda;         // element pitch of A (or of its kept values)
-  const uint8_t* Am;   // OP_SP / OP_TSP metadata
+  const uint8_t* Am;   // OP_SP metadata
   int64_t ldam;        // byte pitch of the metadata
-  const uint16_t* B;   // OP_K [N x K], OP_T [K x N]
+  const uint16_t* B;   // [N x K]
   int64_t ldb;
   // b_nsk > 0: B (OP_K) is blocked (blocked_index below) with b_nsk K blocks
   // per row panel, zero-padded, and ldb is 64; every B load is unchecked.
@@ -103,15 +93,9 @@ struct GemmArgs {
   // contiguous panels (XCD x takes panel x % m_groups and a share of the N
   // tiles), so that the A rows a panel needs stay resident in the XCD's L2.
   int m_groups;
-  // Stream-K (register-staged path, EPI_F32): when stream_steps > 0, the
-  // gridDim.x workgroups split the tiles x stream_steps K steps into equal
-  // contiguous ranges; workgroup w writes the partial tile of the j-th tile
-  // its range touches to C + (w * stream_segs + j) * BM * BN (row-major).
-  int64_t stream_steps;
-  int stream_segs;
   // Compressed 2:4 tensors in the tiled layout (tiled_index below): the 2:4
-  // operand of OP_SP when a_tiled is set (OP_TSP and the staged epilogues
-  // always), with tok token rows.
+  // operand of OP_SP when a_tiled is set (the staged epilogues always), with
+  // tok token rows.
   int a_tiled;
   int64_t tok;
 };
@@ -168,13 +152,6 @@ struct GemmCfg {
   // lane accumulates runs of consecutive C columns (plain bf16 / fp32 output,
   // written with 16-byte stores).  The 2:4 operand must stay first.
   static constexpr bool SWAP = !SPARSE && (EPI_ == EPI_BF16 || EPI_ == EPI_F32);
-  // K-major operands ([K x rows] in memory) are staged K-major in LDS and read
-  // with the transposing ds_read_b64_tr_b16.
-  static constexpr bool A_KM = AMODE_ == OP_T || AMODE_ == OP_TSP;
-  static constexpr bool B_KM = BMODE_ == OP_T;
-  // DIRECT: every operand goes global -> LDS by DMA; otherwise (the 2:4
-  // K-major operand, expanded in registers) A is register-staged.
-  static constexpr bool DIRECT = AMODE_ != OP_TSP;
   static constexpr int STAGES = STAGES_;
   // dense contraction per step: 64, or SPK (64 or 128) for a 2:4 operand
   static constexpr int BK = SPARSE ? SPK_ : 64;
@@ -191,8 +168,6 @@ struct GemmCfg {
   static constexpr int FM = TM / 32, FN = TN / 32;
   static_assert(NW == 4 || NW == 8, "4 or 8 waves");
   static_assert(TM % 32 == 0 && TN % 32 == 0, "wave tile must be a multiple of 32");
-  static_assert(DIRECT || STAGES_ == 2, "register staging uses two LDS buffers");
-  static_assert(!(A_KM || B_KM) || !SPARSE, "2:4 along K with a K-major partner is not used");
   static_assert(STAGES_ >= 2 && STAGES_ <= 4, "2 to 4 stages");
   // The compressed-activation epilogues stage a BN x BM/2 tile of kept values
   // in one stage buffer and the metadata rows (BM/8 bytes + 4 pad) after the
@@ -210,14 +185,13 @@ struct GemmCfg {
   static constexpr int LDS_BYTES = DEEP_ == 1   ? 3 * A_PART + 2 * B_BYTES
                                    : DEEP_ == 2 ? 2 * A_PART + 3 * B_BYTES
                                                 : STAGES_ * STAGE + (STAGED_EPI ? META_BYTES : 0);
-  static_assert(DEEP_ == 0 || (STAGES_ == 2 && !STAGED_EPI && DIRECT), "three-stage ring: plain epilogues, direct staging");
-  static_assert(!STAGED_EPI || (BM_ == 256 && BN_ * BM_ <= STAGE && DIRECT), "staged epilogue layout");
+  static_assert(DEEP_ == 0 || (STAGES_ == 2 && !STAGED_EPI), "three-stage ring: plain epilogues, direct staging");
+  static_assert(!STAGED_EPI || (BM_ == 256 && BN_ * BM_ <= STAGE), "staged epilogue layout");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS");
-  static_assert(EPI_ != EPI_DH_STE || AMODE_ != OP_TSP, "two operand pairs: direct staging");
   // a blocked B (GemmArgs::b_nsk) needs 128-byte LDS rows of B (64 K per
   // step); only the plain-output products take one, and the other kernels are
   // compiled without the branch
-  static constexpr bool B_BLOCKABLE = !B_KM && B_ROWB == 128 && (EPI_ == EPI_BF16 || EPI_ == EPI_F32);
+  static constexpr bool B_BLOCKABLE = B_ROWB == 128 && (EPI_ == EPI_BF16 || EPI_ == EPI_F32);
 };
 
 // LDS chunk swizzle.  Fragment reads touch 8 consecutive rows at one chunk;
@@ -329,6 +303,8 @@ __device__ __forceinline__ void wait_vmcnt() {
 // the explicit vmcnt waits; the empty memory clobber keeps the compiler from
 // moving LDS reads across it).
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_barrier" ::: "memory"); }
+// The same after this wave's own LDS operations have finished.
+__device__ __forceinline__ void lds_wait_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // A [ROWS x ROWB] K-contiguous tile (or the kept values of a 2:4 tile) copied
 // by DMA: the tile is cut into 1 KB blocks (8 or 4 rows), PER_WAVE blocks per
@@ -420,173 +396,6 @@ struct DmaMeta {
     for (int j = J0; j < J1; ++j) dma_b32_s(sbase, voff[j], lds + (wave * PER_WAVE + j) * 256);
   }
 };
-
-// ---- K-major tiles ----------------------------------------------------------
-// A K-major operand (stored [K x rows], rows contiguous) is staged as it is:
-// LDS row k (one per contraction index of the step, 64 of them) holds the
-// tile's ROWS elements, in 32-byte chunks of 16 elements; chunk c of row k
-// sits at chunk position c ^ 2 (k & 3).
-//
-// ds_read_b64_tr_b16 (gfx950, pinned by a probe): within each group of 16
-// lanes, lane j reads 4 consecutive 16-bit elements; lane i of the group then
-// receives element i % 4 of lane 4q + i/4's read, for q = 0..3.  When lane j
-// reads row k0 + j/4 at columns c0 + 4 (j % 4), lane i therefore receives
-// column c0 + i of rows k0..k0+3: one MFMA fragment half.  The 32 lanes
-// served together touch rows k0..k0+3 at two adjacent logical chunks (c even,
-// c + 1); the swizzle spreads these eight 32-byte pieces over eight distinct
-// positions, i.e. all 64 banks (each row is a multiple of 256 bytes).
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ int km_swz(int k, int chunk) { return chunk ^ ((k & 3) << 1); }
-
-// Fragment of a v_mfma_f32_32x32x16_bf16 operand from a K-major LDS tile:
-// lane l gets columns col0 + l % 32, contraction indices 16 kk + 8 (l / 32) + 0..7.
-template <int ROWS>
-__device__ __forceinline__ bf16x8 frag_km(const char* base, int kk, int col0, int lane) {
-  constexpr int ROWB = ROWS * 2;
-  const int grp = lane >> 4, j = lane & 15;
-  const int k = kk * 16 + 8 * (grp >> 1) + (j >> 2);
-  const int col = col0 + 16 * (grp & 1) + 4 * (j & 3);
-  const int c = col >> 4, w = (col & 15) * 2;
-  const char* p0 = base + k * ROWB + (km_swz(k, c) << 5) + w;
-  const char* p1 = base + (k + 4) * ROWB + (km_swz(k + 4, c) << 5) + w;
-  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p0);
-  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p1);
-  const s16x4 lo = a, hi = b;
-  typedef short s16x8 __attribute__((ext_vector_type(8)));
-  const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  return __builtin_bit_cast(bf16x8, v);
-}
-
-// A dense K-major tile [64 x ROWS] copied by DMA: 1 KB blocks, PER_WAVE per
-// wave; lane i fills the block's 16-byte unit i, i.e. physical unit (i mod
-// units per row) of row (block rows + i / units per row), and fetches the
-// global 8 elements that the swizzle maps there.
-template <int ROWS, int NW>
-struct DmaTileKM {
-  static constexpr int ROWB = ROWS * 2;
-  static constexpr int BLOCKS = 64 * ROWB / 1024;
-  static constexpr int PER_WAVE = BLOCKS / NW;
-  static_assert(BLOCKS % NW == 0 && ROWB <= 1024, "blocks per wave");
-  template <int J0, int J1>
-  __device__ __forceinline__ static void issue(const uint16_t* __restrict__ p, int64_t ld, int64_t col0,
-                                               int64_t cols_valid, int64_t k0, int64_t k_valid, uint32_t lds,
-                                               int wave, int lane) {
-#pragma unroll
-    for (int j = J0; j < J1; ++j) {
-      const int blk = wave * PER_WAVE + j;
-      const int off = blk * 1024 + lane * 16;
-      const int k = off / ROWB, pu = (off % ROWB) / 16;
-      const int col = km_swz(k, pu >> 1) * 16 + (pu & 1) * 8;
-      const int64_t gk = k0 + k, gc = col0 + col;
-      const void* src = (gk < k_valid && gc < cols_valid) ? (const void*)(p + gk * ld + gc) : (const void*)g_dma_zero;
-      dma_b128(src, __builtin_amdgcn_readfirstlane(lds + blk * 1024));
-    }
-  }
-  __device__ __forceinline__ static uint32_t lane_off(int j, int64_t ld, int wave, int lane) {
-    const int blk = wave * PER_WAVE + j;
-    const int off = blk * 1024 + lane * 16;
-    const int k = off / ROWB, pu = (off % ROWB) / 16;
-    const int col = km_swz(k, pu >> 1) * 16 + (pu & 1) * 8;
-    return (uint32_t)k * (uint32_t)(ld * 2) + (uint32_t)col * 2u;
-  }
-  __device__ __forceinline__ static const char* step_base(const uint16_t* p, int64_t ld, int64_t col0, int64_t k0) {
-    return (const char*)(p + k0 * ld + col0);
-  }
-  template <int J0, int J1>
-  __device__ __forceinline__ static void issue_fast(const char* sbase, const uint32_t* voff, uint32_t lds, int wave) {
-#pragma unroll
-    for (int j = J0; j < J1; ++j) dma_b128_s(sbase, voff[j], lds + (wave * PER_WAVE + j) * 1024);
-  }
-};
-
-// A 2:4 K-major tile: rows of kept values [K x cols/2] + metadata [K x cols/8]
-// (the compressed activation read along tokens).  Each thread loads the kept
-// values (16 bytes) and codes (2 bytes) of 16 consecutive features of one
-// contraction row, and after the current step's MFMAs writes them expanded
-// (32 bytes) into the K-major LDS tile; no transpose is needed.
-template <int ROWS, int NT>
-struct StagerKMSP {
-  static constexpr int ROWB = ROWS * 2;
-  static constexpr int CHUNKS = ROWS / 16;
-  static constexpr int NU = 64 * CHUNKS / NT;
-  static_assert((64 * CHUNKS) % NT == 0, "units per thread");
-  // Unit q (16 features of one contraction row): chunk q % 4 of entry block
-  // q / 256 (64 features) at row (q / 4) % 64, so that the 64 lanes of a wave
-  // read 16 rows x 64 bytes of one entry block, 1 KB contiguous in the tiled
-  // layout.
-  __device__ __forceinline__ static int unit_k(int q) { return (q >> 2) & 63; }
-  __device__ __forceinline__ static int unit_c(int q) { return (q >> 8) * 4 + (q & 3); }
-  uint4 v[NU];
-  uint16_t m[NU];
-  // The compressed tensor is in the tiled layout with tok rows (tokens =
-  // contraction rows here).
-  // The step's rows k0 .. k0+63 lie in one block of 256 rows (R of them
-  // exist), so every piece is a 32-bit offset from the step's block start.
-  __device__ __forceinline__ void load(const uint16_t* __restrict__ pv, int64_t ldv, const uint8_t* __restrict__ pm,
-                                       int64_t ldm, int64_t col0, int64_t cols_valid, int64_t k0, int64_t k_valid,
-                                       int tid, int64_t tok) {
-    const int64_t tb0 = k0 & ~(int64_t)255;
-    const int R = (int)(tok - tb0 < 256 ? tok - tb0 : 256);
-    const uint16_t* vb = pv + tiled_step<32>(k0, col0, tok, ldv);
-    const uint8_t* mb = pm + tiled_step<8>(k0, col0, tok, ldm);
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int q = u * NT + tid, k = unit_k(q), c = unit_c(q);
-      const int64_t gk = k0 + k, f = col0 + 16 * c;
-      v[u] = make_uint4(0u, 0u, 0u, 0u);
-      m[u] = 0u;
-      if (gk < k_valid && f < cols_valid) {
-        v[u] = *(const uint4*)(vb + ((c >> 2) * R * 32 + k * 32 + (c & 3) * 8));
-        m[u] = *(const uint16_t*)(mb + ((c >> 2) * R * 8 + k * 8 + (c & 3) * 2));
-      }
-    }
-  }
-  // Unchecked path (tile and step inside the matrix, step inside a full block
-  // of 256 rows): per-lane byte offsets from the step's block start
-  // (tiled_step of its first row and the tile's first column), constant over
-  // the steps, and a wave-uniform base per step.  Thread unit (k, c) reads
-  // entry block c / 4 at row k, entries 8 (c % 4) .. (values) and 2 (c % 4) ..
-  // (metadata bytes).
-  __device__ __forceinline__ static void lane_offs(int tid, uint32_t (&ov)[NU], uint32_t (&om)[NU]) {
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int q = u * NT + tid, k = unit_k(q), c = unit_c(q);
-      ov[u] = (uint32_t)((c >> 2) * 256 * 32 + k * 32 + (c & 3) * 8) * 2u;
-      om[u] = (uint32_t)((c >> 2) * 256 * 8 + k * 8 + (c & 3) * 2);
-    }
-  }
-  __device__ __forceinline__ void load_fast(const char* vbase, const char* mbase, const uint32_t (&ov)[NU],
-                                            const uint32_t (&om)[NU]) {
-    const char* vb = (const char*)uniform_ptr(vbase);
-    const char* mb = (const char*)uniform_ptr(mbase);
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const u32x4 x = *(const __attribute__((address_space(1))) u32x4*)(vb + ov[u]);
-      v[u] = make_uint4(x[0], x[1], x[2], x[3]);
-      m[u] = *(const __attribute__((address_space(1))) uint16_t*)(mb + om[u]);
-    }
-  }
-  __device__ __forceinline__ void store(char* lds, int tid) const {
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int q = u * NT + tid, k = unit_k(q), c = unit_c(q);
-      char* dst = lds + k * ROWB + (km_swz(k, c) << 5);
-      *(uint4*)dst = expand2(make_uint2(v[u].x, v[u].y), m[u] & 0xFFu);
-      *(uint4*)(dst + 16) = expand2(make_uint2(v[u].z, v[u].w), m[u] >> 8);
-    }
-  }
-};
-
-// XCD-aware placement: consecutive workgroup ids go to different XCDs (8 on
-// MI355X), so remap them so that each XCD receives a contiguous range of
-// logical tiles, which then share operand rows in that XCD's L2.
-__device__ __forceinline__ int xcd_remap(int pid, int total) {
-  constexpr int kXcd = 8;
-  const int full = total / kXcd * kXcd;
-  if (pid >= full) return pid;
-  return (pid % kXcd) * (full / kXcd) + pid / kXcd;
-}
 
 // Persistent schedule of the direct-staged kernels: the grid holds at most
 // one workgroup per CU, and workgroup b runs tiles first, first + stride, ...
@@ -694,21 +503,13 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
       auto read = [&](int kk, int slot) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
-          if constexpr (Cfg::A_KM) {
-            af[slot][i] = frag_km<BM>(lA, kk, wm * TM + i * 32, lane);
-          } else {
-            const int row = wm * TM + i * 32 + lrow;
-            af[slot][i] = *(const bf16x8*)(lA + row * 128 + swz(row, 2 * kk + lhalf) * 16);
-          }
+          const int row = wm * TM + i * 32 + lrow;
+          af[slot][i] = *(const bf16x8*)(lA + row * 128 + swz(row, 2 * kk + lhalf) * 16);
         }
 #pragma unroll
         for (int j = 0; j < FN; ++j) {
-          if constexpr (Cfg::B_KM) {
-            bfr[slot][j] = frag_km<BN>(lB, kk, wn * TN + j * 32, lane);
-          } else {
-            const int row = wn * TN + j * 32 + lrow;
-            bfr[slot][j] = *(const bf16x8*)(lB + row * 128 + swz(row, 2 * kk + lhalf) * 16);
-          }
+          const int row = wn * TN + j * 32 + lrow;
+          bfr[slot][j] = *(const bf16x8*)(lB + row * 128 + swz(row, 2 * kk + lhalf) * 16);
         }
       };
       if constexpr (Cfg::PIPE) read(0, 0);
@@ -785,9 +586,8 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
 
   // ---------------------------------------------------------------- epilogues
   // Writes the tile at (m0, n0); `stage` is an LDS stage buffer that no copy
-  // is filling (the staged epilogues use it).  EPI_F32 writes a stream-K
-  // partial tile to f32_slot when it is set, else the split's partial rows.
-  float* f32_slot = nullptr;
+  // is filling (the staged epilogues use it).  EPI_F32 writes the split's
+  // partial rows.
   // `pre` runs in the staged epilogues once every wave has finished the
   // main loop's LDS reads (EPI_DH with PRE_S: it issues the next tile's first
   // loads and waits for the S tile copied during the last K step).
@@ -827,13 +627,6 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
               for (int c = 0; c < 2; ++c)
                 if (col + 8 * c < g.N) *(uint4*)(dst + 8 * c) = make_uint4(out[c][0], out[c][1], out[c][2], out[c][3]);
             }
-          } else if (f32_slot != nullptr) {
-            // stream-K partial: the whole tile, tile-local rows and columns
-            float* dst = f32_slot + (row - m0) * BN + (colb - n0);
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-              *(float4*)(dst + 8 * b + 4 * lhalf) =
-                  make_float4(acc[i][j][4 * b], acc[i][j][4 * b + 1], acc[i][j][4 * b + 2], acc[i][j][4 * b + 3]);
           } else {
             float* part = (float*)g.C + (int64_t)by * g.M * g.N;
             if (row < g.M) {
@@ -1159,9 +952,9 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
     }
   };
 
-  if constexpr (Cfg::DIRECT) {
-    using TA = std::conditional_t<Cfg::A_KM, DmaTileKM<BM, NW>, DmaTile<BM, Cfg::A_ROWB, SPARSE, NW>>;
-    using TB = std::conditional_t<Cfg::B_KM, DmaTileKM<BN, NW>, DmaTile<BN, Cfg::B_ROWB, false, NW>>;
+  {
+    using TA = DmaTile<BM, Cfg::A_ROWB, SPARSE, NW>;
+    using TB = DmaTile<BN, Cfg::B_ROWB, false, NW>;
     using TMeta = DmaMeta<BM, (SPARSE ? Cfg::M_ROWB : 256), (SPARSE ? NW : 1)>;
     constexpr int LA = TA::PER_WAVE, LB = TB::PER_WAVE, LM = SPARSE ? TMeta::PER_WAVE : 0;
     constexpr int LOADS = LA + LB + LM;   // DMA instructions per wave per step
@@ -1604,125 +1397,6 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
         has_next = next < tr.end;
         load_next();
       }
-    }
-  } else {
-    // A: the 2:4 K-major operand, expanded in registers; B: DMA.  The next
-    // step's A loads and B DMA are issued before the current step's MFMAs; A
-    // is written to LDS after them; one barrier per step.
-    using TB = std::conditional_t<Cfg::B_KM, DmaTileKM<BN, NW>, DmaTile<BN, Cfg::B_ROWB, false, NW>>;
-    const uint32_t smem_lds = lds_u32(smem);
-    uint32_t offB[TB::PER_WAVE];
-#pragma unroll
-    for (int j = 0; j < TB::PER_WAVE; ++j) offB[j] = TB::lane_off(j, g.ldb, wave, lane);
-
-    // Accumulate steps [0, ns) of the K range starting at kb of the tile at (m0, n0).
-    auto run_tile = [&](int64_t m0, int64_t n0, int64_t kb, int ns) __attribute__((always_inline)) {
-      zero_acc();
-      StagerKMSP<BM, NT> sa;
-      int b_steps_in = 0;   // steps whose B loads need no bounds checks
-      if (n0 + BN <= g.N) {
-        const int64_t k_in = g.kb_valid - kb;
-        b_steps_in = k_in <= 0 ? 0 : (int)(k_in / BK < ns ? k_in / BK : ns);
-      }
-      b_steps_in = __builtin_amdgcn_readfirstlane(b_steps_in);
-      int a_steps_in = 0;   // steps whose A loads need no bounds checks (and lie in full row blocks)
-      if (m0 + BM <= g.m_valid) {
-        const int64_t k_full = g.ka_valid < (g.tok & ~(int64_t)255) ? g.ka_valid : (g.tok & ~(int64_t)255);
-        const int64_t k_in = k_full - kb;
-        a_steps_in = k_in <= 0 ? 0 : (int)(k_in / BK < ns ? k_in / BK : ns);
-      }
-      a_steps_in = __builtin_amdgcn_readfirstlane(a_steps_in);
-      // Copy cursors (the scalar code of eight waves shares one scalar unit,
-      // so the unchecked steps avoid the general address arithmetic).  In
-      // the tiled layout a step's 64 token rows of kept values (metadata) lie
-      // 4096 (512) bytes after the previous step's inside a 256-row block; at
-      // a block boundary the next block's rows follow 512 lda - 3 * 4096
-      // (256 ldam - 3 * 512) bytes on (full blocks: R = 256).  B advances BK
-      // rows (K-major) or BK elements.
-      static_assert(BK == 64, "64 token rows per step");
-      const char* cv = (const char*)uniform_ptr(g.A + tiled_step<32>(kb, m0, g.tok, g.lda));
-      const char* cm = (const char*)uniform_ptr(g.Am + tiled_step<8>(kb, m0, g.tok, g.ldam));
-      const int64_t jv = uniform_i64(512 * g.lda - 3 * 4096), jm = uniform_i64(256 * g.ldam - 3 * 512);
-      uint32_t tpos = __builtin_amdgcn_readfirstlane((uint32_t)(kb & 255));   // token row in its block of the next load
-      const char* cb = (const char*)uniform_ptr(TB::step_base(g.B, g.ldb, n0, kb));
-      const uint32_t sb = __builtin_amdgcn_readfirstlane((uint32_t)(TB::step_base(g.B, g.ldb, n0, kb + BK) - TB::step_base(g.B, g.ldb, n0, kb)));
-      auto load_a = [&](int step) __attribute__((always_inline)) {
-        const int64_t k0 = kb + (int64_t)step * BK;
-        if (step < a_steps_in) {
-          // per-lane offsets formed here from a laundered thread index (cheaper
-          // than keeping them in registers across the main loop)
-          uint32_t aov[StagerKMSP<BM, NT>::NU], aom[StagerKMSP<BM, NT>::NU];
-          int tc = tid;
-          asm volatile("" : "+v"(tc));
-          StagerKMSP<BM, NT>::lane_offs(tc, aov, aom);
-          sa.load_fast(cv, cm, aov, aom);
-          tpos = (tpos + 64) & 255;
-          const bool cross = tpos == 0;
-          cv += cross ? jv : 4096;
-          cm += cross ? jm : 512;
-        } else {
-          int64_t kc = uniform_i64(k0);   // addresses formed afresh (see the direct path)
-          int tc = tid;
-          asm volatile("" : "+s"(kc), "+v"(tc));
-          sa.load(g.A, g.lda, g.Am, g.ldam, m0, g.m_valid, kc, g.ka_valid, tc, g.tok);
-        }
-      };
-      auto issue_b = [&](int step) __attribute__((always_inline)) {
-        const int64_t k0 = kb + (int64_t)step * BK;
-        const uint32_t base = smem_lds + (uint32_t)((step & 1) * Cfg::STAGE) + Cfg::A_BYTES;
-        if (step < b_steps_in) {
-          TB::template issue_fast<0, TB::PER_WAVE>(cb, offB, base, wave);
-          cb += sb;
-        } else
-          TB::template issue<0, TB::PER_WAVE>(g.B, g.ldb, n0, g.N, k0, g.kb_valid, base, wave, lane);
-      };
-      if (ns > 0) {
-        load_a(0);
-        issue_b(0);
-        sa.store(smem, tid);
-        wait_vmcnt<0>();
-        __syncthreads();
-      }
-      for (int s = 0; s < ns; ++s) {
-        const int buf = s & 1;
-        const bool more = s + 1 < ns;
-        if (more) {
-          load_a(s + 1);
-          issue_b(s + 1);
-        }
-        // The expanded A of step s+1 is written to the other buffer (last
-        // read in step s-1, before the previous barrier) ahead of this step's
-        // last MFMA sub-step, so that its VALU work overlaps the MFMAs still
-        // in flight.  (Measured: 5 % faster than after the step; earlier
-        // sub-steps wait longer for A's loads or spill.)
-        compute(smem + buf * Cfg::STAGE, smem + buf * Cfg::STAGE + Cfg::A_PART, [&](int kk) {
-          if (kk == 3 && more) sa.store(smem + (buf ^ 1) * Cfg::STAGE, tid);
-        });
-        wait_vmcnt<0>();   // B's DMA of step s+1 has landed
-        __syncthreads();   // A's LDS writes and B's DMA of step s+1 are complete
-      }
-    };
-    int64_t m0, n0;
-    if (g.stream_steps > 0) {
-      // Stream-K: this workgroup's share [beg, end) of the tiles x S steps,
-      // one partial tile per tile it touches.
-      const int64_t S = g.stream_steps, I = (int64_t)ntiles * S;
-      const int64_t beg = (int64_t)blockIdx.x * I / gridDim.x, end = (int64_t)(blockIdx.x + 1) * I / gridDim.x;
-      const int64_t t_first = beg / S;
-      for (int64_t it = beg; it < end;) {
-        const int t = (int)(it / S);
-        const int64_t k_first = it - (int64_t)t * S;
-        const int64_t k_last = end - (int64_t)t * S < S ? end - (int64_t)t * S : S;
-        origin(t, m0, n0);
-        run_tile(m0, n0, k_first * BK, (int)(k_last - k_first));
-        f32_slot = (float*)g.C + ((int64_t)blockIdx.x * g.stream_segs + (t - t_first)) * (BM * BN);
-        epilogue(m0, n0, smem, [] {});
-        it = (int64_t)t * S + k_last;
-      }
-    } else {
-      origin(xcd_remap(bx, ntiles), m0, n0);
-      run_tile(m0, n0, kbeg, nsteps);
-      epilogue(m0, n0, smem, [] {});
     }
   }
 }

@@ -104,11 +104,18 @@ __global__ __launch_bounds__(KP == 8 ? 512 : 256, 2) void resident_kernel(const 
   const int f_begin = (int)((int64_t)fs * g.nfb / g.fsplit), f_end = (int)((int64_t)(fs + 1) * g.nfb / g.fsplit);
   const int t_end = (int)(g.T - n0 < 128 ? g.T - n0 : 128);   // tokens of this block
 
-  using TX = DmaTile<128, 128, false, NW>;
+  // The token block -> LDS: panel q's row t holds its 8 chunks of 16 bytes, chunk
+  // c at position c ^ (t / 2) % 8: the rows and chunks a fragment read serves
+  // together (below) then lie in distinct banks.  Rows past the last token are 0.
   const uint32_t smem_lds = lds_u32(smem);
-  for (int q = 0; q < KP; ++q)
-    TX::template issue<0, TX::PER_WAVE>(g.X, g.ldx, n0, g.T, (int64_t)q * 64, KP * 64, smem_lds + q * PANEL, wave, lane);
-
+  for (int q = 0; q < KP; ++q) {
+#pragma unroll
+    for (int k = 0; k < 16 / NW; ++k) {
+      const int blk = wave * (16 / NW) + k, row = blk * 8 + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
+      const void* src = row < t_end ? (const void*)(g.X + (n0 + row) * g.ldx + q * 64 + c * 8) : (const void*)g_dma_zero;
+      dma_b128(src, __builtin_amdgcn_readfirstlane(smem_lds + q * PANEL + blk * 1024));
+    }
+  }
   if constexpr (COUNTER) {
     if (tid == 0) s_next = f_begin + NW;
   }
@@ -129,18 +136,16 @@ __global__ __launch_bounds__(KP == 8 ? 512 : 256, 2) void resident_kernel(const 
   __syncthreads();
   if (cur >= f_end) return;
 
-  // Token fragments: row 16 j + l % 16 of a panel, chunk 4 kk + l / 16,
-  // swizzled as swz(): over j and kk the same four chunk positions in turn.
+  // Token fragments: row 16 j + l % 16 of a panel, chunk 4 kk + l / 16.
   const int l16 = lane & 15, lg = lane >> 4;
   bf16x8 bf[2][4];
-  const char* xb[4];
+  const char* xb[2];
 #pragma unroll
-  for (int x = 0; x < 4; ++x) xb[x] = smem + l16 * 128 + ((lg ^ 2 * x) ^ (l16 & 7) ^ (l16 >> 3)) * 16;
+  for (int x = 0; x < 2; ++x) xb[x] = smem + l16 * 128 + ((lg | 4 * x) ^ (l16 >> 1)) * 16;
   // sub-step s of a panel: k32 step s / 2, tokens 64 (s % 2) .. + 63
   auto read_b = [&](int q, int s, int slot) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      bf[slot][j] = *(const bf16x8*)(xb[j ^ (2 * (s >> 1))] + q * PANEL + (4 * (s & 1) + j) * 2048);
+    for (int j = 0; j < 4; ++j) bf[slot][j] = *(const bf16x8*)(xb[s >> 1] + q * PANEL + (4 * (s & 1) + j) * 2048);
   };
   f32x4 acc[4][8];
   auto panel = [&](auto first, auto last, int q, const u32x4* np) __attribute__((always_inline)) {
