@@ -7,6 +7,7 @@
 
 #include "gemm.h"
 #include "internal.h"
+#include "plain.h"
 #include "resident.h"
 #include "small.h"
 #include "wgrad.h"
@@ -171,9 +172,6 @@ hipError_t fill_zero(float* p, int64_t n, hipStream_t st) {
 // Dense products with both operands K-contiguous: 256 x BN tiles, 4 x 2 waves.
 template <int BN, int EPI, bool M_FAST, int DEEP = 0>
 using CfgNT = GemmCfg<256, BN, 4, 2, OP_K, OP_K, EPI, M_FAST, 2, true, false, 128, DEEP>;
-// Plain bf16 outputs (A = the token-major activation streaming from HBM, B =
-// a weight factor resident in L2): A gets three LDS stages, B two.
-using CfgNT3 = CfgNT<256, EPI_BF16, false, 1>;
 // 2:4 sparse A (smfmac) times K-contiguous B: 256 x 256 tiles, 4 x 2 waves
 // (64 x 128 per wave), 64 dense K per step in three LDS stages (150 KB).  The
 // full-width N tile halves the re-reads of the compressed operand, which
@@ -207,16 +205,42 @@ hipError_t launch(const char* tag, GemmArgs g, int splits, hipStream_t st) {
   // looping over its tiles.
   const int tiles = g.tiles_m * g.tiles_n;
   const int cus = device_cus();
-  const int wgs = tiles > cus ? cus : tiles;
+  const int slots = cus * (Cfg::LDS_BYTES <= 80 * 1024 ? 2 : 1);
+  const int wgs = tiles > slots ? slots : tiles;
   const dim3 grid((unsigned)wgs, (unsigned)splits);
   TimedLaunch tl(tag, st);
   hipLaunchKernelGGL(gemm_kernel<Cfg>, grid, dim3(Cfg::NT), 0, st, g);
   return hipGetLastError();
 }
 
+// Dense products (plain.h): 256 x 256 tiles on 8 waves with the streaming operand
+// three steps deep, 256 x 128 for narrow outputs; 128 x 128 on 4 waves, two
+// workgroups per CU.
+using PlainNT = PlainCfg<256, 256, 4, 2, false, 3, 2>;
+using PlainNTn = PlainCfg<256, 128, 4, 2, false, 3, 3>;
+template <bool F32>
+using PlainNTs = PlainCfg<128, 128, 2, 2, F32, 3, 2>;
+
+template <class Cfg>
+hipError_t launch_plain(const char* tag, GemmArgs g, int splits, hipStream_t st) {
+  if (g.b_nsk > 0 && g.ldb != 64) return hipErrorInvalidValue;
+  g.tiles_m = (int)cdiv(g.M, Cfg::BM);
+  g.tiles_n = (int)cdiv(g.N, Cfg::BN);
+  if (splits <= 1) {
+    splits = 1;
+    g.k_split = cdiv(g.K, Cfg::BK) * Cfg::BK;
+  }
+  const int tiles = g.tiles_m * g.tiles_n, slots = device_cus() * (Cfg::LDS <= 80 * 1024 ? 2 : 1);
+  TimedLaunch tl(tag, st);
+  hipLaunchKernelGGL(plain_kernel<Cfg>, dim3((unsigned)std::min(tiles, slots), (unsigned)splits), dim3(Cfg::NT), 0, st, g);
+  return hipGetLastError();
+}
+
 // Small problems: when 256-wide tiles would leave more than a quarter of the
 // CUs without a tile, 128 x 128 tiles (4 waves of 64 x 64) give four times as
 // many (twice as many for the staged 2:4 epilogues, which need 256 features).
+// In between: 256 x 128 tiles on 8 waves (64 x 64 per wave), four stages (136 KB).
+using CfgSPn = GemmCfg<256, 128, 4, 2, OP_SP, OP_K, EPI_BF16, false, 4, true, false, 64>;
 using CfgSPs = GemmCfg<128, 128, 2, 2, OP_SP, OP_K, EPI_BF16, false, 3, true, false, 64>;
 
 bool few_tiles(int64_t M, int64_t N, int bm, int bn) { return cdiv(M, bm) * cdiv(N, bn) * 4 < 3LL * device_cus(); }
@@ -268,8 +292,15 @@ hipError_t launch_sp(const char* tag, GemmArgs g, hipStream_t st, float* part = 
       if (e != hipSuccess) return e;
       return reduce_bf16(part, p.splits, g.M, g.N, out, ldo, st);
     }
-    return launch<CfgSPs>(tag, g, 1, st);
   }
+  // Microseconds per K step of one round of tiles (measured at 86 steps: 256 x 256
+  // 215 us in two rounds, 256 x 128 86 us, 128 x 128 99 us with two workgroups per
+  // CU and 44 us with one): the tiling with the least total.
+  const int64_t cus = device_cus(), t128 = cdiv(g.M, 128) * cdiv(g.N, 128), last = t128 % (2 * cus);
+  const double big = 1.25 * cdiv(cdiv(g.M, 256) * cdiv(g.N, 256), cus), mid = 1.0 * cdiv(cdiv(g.M, 256) * cdiv(g.N, 128), cus);
+  const double small = 1.15 * (t128 / (2 * cus)) + (last == 0 ? 0.0 : last <= cus ? 0.51 : 1.15);
+  if (small < mid && small < big) return launch<CfgSPs>(tag, g, 1, st);
+  if (mid < big) return launch<CfgSPn>(tag, g, 1, st);
   return launch<CfgSP>(tag, g, 1, st);
 }
 // Epilogues that select and compress 2:4 groups (features along M).
@@ -440,14 +471,15 @@ hipError_t gemm_nt_bf16(const char* tag, const uint16_t* A, int64_t lda, const u
       g.C = part;
       g.ldc = N;
       g.k_split = p.k_split;
-      const hipError_t e = launch<CfgNTs<EPI_F32, false>>(tag, g, p.splits, st);
+      
+      const hipError_t e = launch_plain<PlainNTs<true>>(tag, g, p.splits, st);
       if (e != hipSuccess) return e;
       return reduce_bf16(part, p.splits, M, N, C, ldc, st);
     }
-    return launch<CfgNTs<EPI_BF16, false>>(tag, g, 1, st);
+    return launch_plain<PlainNTs<false>>(tag, g, 1, st);
   }
-  if (N <= 128) return launch<CfgNT<128, EPI_BF16, false>>(tag, g, 1, st);
-  return launch<CfgNT3>(tag, g, 1, st);
+  if (N <= 128) return launch_plain<PlainNTn>(tag, g, 1, st);
+  return launch_plain<PlainNT>(tag, g, 1, st);
 }
 
 // Weight gradients (wgrad.h): the jobs of one backward and how their (tile, step)

@@ -1,6 +1,7 @@
 // Tiled MFMA GEMM for gfx950 (CDNA4): C = A * B with bf16 operands and fp32
-// accumulation, one template covering every product of the ELAS low-rank FFN
-// (forward and backward).
+// accumulation, the template of the 2:4 sparse x dense products and, where the
+// token-resident kernel does not apply, of the products with an activation
+// epilogue; and the LDS copies and layouts the other kernels share.
 //
 // Tiling: a workgroup of WAVES_M x WAVES_N wave64s owns a BM x BN tile of C.
 // The contraction runs in steps of BK (64 dense, or 128 dense = 64 kept
@@ -44,8 +45,8 @@ typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 enum OpMode { OP_K = 0, OP_SP = 2 };
 enum EpiMode {
-  EPI_BF16 = 0,       // C bf16
-  EPI_F32 = 1,        // fp32 split-K partials
+  EPI_BF16 = 0,       // C bf16 (here: 2:4 products)
+  EPI_F32 = 1,        // fp32 split-K partials (here: 2:4 products)
   EPI_SPARSIFY = 2,   // ReLU^2 + top-2 of 4 + compressed write (C = H^T)
   EPI_DH = 3,         // dH = dS * mask * 2 relu(h), compressed (C = dS^T)
   EPI_ACT_DENSE = 4,  // dense activation: relu(h)^2 (act_square) or relu(h) (C = H^T)
@@ -148,10 +149,6 @@ struct GemmCfg {
   static constexpr int AMODE = AMODE_, BMODE = BMODE_, EPI = EPI_;
   static constexpr bool M_FAST = M_FAST_;   // consecutive tiles walk M (true) or N (false)
   static constexpr bool SPARSE = AMODE_ == OP_SP;
-  // SWAP: the MFMAs take B's fragment as their first operand, so that each
-  // lane accumulates runs of consecutive C columns (plain bf16 / fp32 output,
-  // written with 16-byte stores).  The 2:4 operand must stay first.
-  static constexpr bool SWAP = !SPARSE && (EPI_ == EPI_BF16 || EPI_ == EPI_F32);
   static constexpr int STAGES = STAGES_;
   // dense contraction per step: 64, or SPK (64 or 128) for a 2:4 operand
   static constexpr int BK = SPARSE ? SPK_ : 64;
@@ -207,10 +204,15 @@ __device__ __forceinline__ int swz16(int row, int chunk) { return chunk ^ (row &
 // a 256-byte bank cycle, so the chunk is XOR-ed with (row / 4) % 4 to give 16
 // consecutive rows 16 different 16-byte positions.
 __device__ __forceinline__ int swz4(int row, int chunk) { return chunk ^ ((row >> 2) & 3); }
-template <int ROWB>
+// 128-byte rows read as 16x16x32 fragments (a 16-lane group of LDS covers rows
+// 0..3 and 12..15 at one chunk and rows 4..11 at the next).
+__device__ __forceinline__ int swz_pair(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
+template <int ROWB, bool PAIR = false>
 __device__ __forceinline__ int swz_row(int row, int chunk) {
   static_assert(ROWB == 64 || ROWB == 128 || ROWB == 256, "row size");
-  if constexpr (ROWB == 64)
+  if constexpr (PAIR)
+    return swz_pair(row, chunk);
+  else if constexpr (ROWB == 64)
     return swz4(row, chunk);
   else if constexpr (ROWB == 128)
     return swz(row, chunk);
@@ -310,7 +312,8 @@ __device__ __forceinline__ void lds_wait_barrier() { asm volatile("s_waitcnt lgk
 // by DMA: the tile is cut into 1 KB blocks (8 or 4 rows), PER_WAVE blocks per
 // wave.  Lane i fills LDS chunk position i of its block; it fetches the
 // global chunk that the swizzle maps there.
-template <int ROWS, int ROWB, bool KEPT, int NW>
+// (PAIR: 128-byte rows in the swz_pair order.)
+template <int ROWS, int ROWB, bool KEPT, int NW, bool PAIR = false>
 struct DmaTile {
   static constexpr int BLOCKS = ROWS * ROWB / 1024;
   static constexpr int PER_WAVE = BLOCKS / NW;
@@ -328,7 +331,7 @@ struct DmaTile {
       const int blk = wave * PER_WAVE + j;
       const int off = blk * 1024 + lane * 16;
       const int row = off / ROWB, pos = (off % ROWB) / 16;
-      const int c = swz_row<ROWB>(row, pos);   // the swizzle is an involution in the chunk index
+      const int c = swz_row<ROWB, PAIR>(row, pos);   // the swizzle is an involution in the chunk index
       const int64_t grow = row0 + row, gk = k0 + (int64_t)c * KPC;
       int64_t idx = grow * ld + (KEPT ? gk / 2 : gk);
       if constexpr (KEPT) {
@@ -342,11 +345,12 @@ struct DmaTile {
   // offset of load j's chunk from the tile's first row at the step's first
   // contraction element (constant over the steps), and the issue from a
   // wave-uniform base.
-  __device__ __forceinline__ static uint32_t lane_off(int j, int64_t ld, int wave, int lane) {
+  // (rows from `rows` on read the row before it)
+  __device__ __forceinline__ static uint32_t lane_off(int j, int64_t ld, int wave, int lane, int rows = ROWS) {
     const int blk = wave * PER_WAVE + j;
     const int off = blk * 1024 + lane * 16;
     const int row = off / ROWB, pos = (off % ROWB) / 16;
-    return (uint32_t)row * (uint32_t)(ld * 2) + (uint32_t)swz_row<ROWB>(row, pos) * 16u;
+    return (uint32_t)(row < rows ? row : rows - 1) * (uint32_t)(ld * 2) + (uint32_t)swz_row<ROWB, PAIR>(row, pos) * 16u;
   }
   __device__ __forceinline__ static const char* step_base(const uint16_t* p, int64_t ld, int64_t row0, int64_t k0) {
     return (const char*)(p + row0 * ld + (KEPT ? k0 / 2 : k0));
@@ -382,10 +386,10 @@ struct DmaMeta {
       dma_b32(src, __builtin_amdgcn_readfirstlane(lds + blk * 256));
     }
   }
-  __device__ __forceinline__ static uint32_t lane_off(int j, int64_t ldm, int wave, int lane) {
+  __device__ __forceinline__ static uint32_t lane_off(int j, int64_t ldm, int wave, int lane, int rows = ROWS) {
     const int blk = wave * PER_WAVE + j;
-    const int off = blk * 256 + lane * 4;
-    return (uint32_t)(off / MROWB) * (uint32_t)ldm + (uint32_t)(off % MROWB);
+    const int off = blk * 256 + lane * 4, row = off / MROWB;
+    return (uint32_t)(row < rows ? row : rows - 1) * (uint32_t)ldm + (uint32_t)(off % MROWB);
   }
   __device__ __forceinline__ static const char* step_base(const uint8_t* pm, int64_t ldm, int64_t row0, int64_t k0) {
     return (const char*)(pm + row0 * ldm + k0 / 8);
@@ -529,8 +533,7 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
         for (int i = 0; i < FM; ++i)
 #pragma unroll
           for (int j = 0; j < FN; ++j)
-            acc[i][j] = Cfg::SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[cur][j], af[cur][i], acc[i][j], 0, 0, 0)
-                                  : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[cur][i], bfr[cur][j], acc[i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[cur][i], bfr[cur][j], acc[i][j], 0, 0, 0);
         if constexpr (Cfg::PIN) __builtin_amdgcn_sched_barrier(0);
       }
     } else {
@@ -592,55 +595,7 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
   // main loop's LDS reads (EPI_DH with PRE_S: it issues the next tile's first
   // loads and waits for the S tile copied during the last K step).
   auto epilogue = [&](const int64_t m0, const int64_t n0, char* stage, auto&& pre) __attribute__((always_inline)) {
-    if constexpr (Cfg::SWAP) {
-      // Accumulator 4b+q of lane l is C[row l%32][col 8b + 4h + q] of its 32x32
-      // block (h = l / 32).  N is a multiple of 8, so each 8-column (bf16) or
-      // 4-column (fp32) piece is wholly inside or outside the matrix.
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          const int64_t row = m0 + wm * TM + i * 32 + lrow;
-          const int64_t colb = n0 + wn * TN + j * 32;
-          if constexpr (Cfg::EPI == EPI_BF16) {
-            // pk[b]: columns 8b+4h .. +3 as two bf16 pairs.  One permlane32 swap
-            // per dword gives lane half 0 columns 0..15 and half 1 columns 16..31.
-            uint32_t pk[4][2];
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-              for (int e = 0; e < 2; ++e)
-                pk[b][e] = bf16x2_rne(acc[i][j][4 * b + 2 * e], acc[i][j][4 * b + 2 * e + 1]);
-            uint32_t out[2][4];
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-              for (int e = 0; e < 2; ++e) {
-                const auto sw = __builtin_amdgcn_permlane32_swap(pk[c][e], pk[c + 2][e], false, false);
-                out[c][e] = sw[0];       // half 0: columns 8c + 2e ..; half 1: 16 + 8c + 2e ..
-                out[c][2 + e] = sw[1];   // half 0: columns 8c + 4 + 2e ..; half 1: 16 + 8c + 4 + 2e ..
-              }
-            const int64_t col = colb + 16 * lhalf;
-            if (row < g.M) {
-              __bf16* dst = (__bf16*)g.C + row * g.ldc + col;
-#pragma unroll
-              for (int c = 0; c < 2; ++c)
-                if (col + 8 * c < g.N) *(uint4*)(dst + 8 * c) = make_uint4(out[c][0], out[c][1], out[c][2], out[c][3]);
-            }
-          } else {
-            float* part = (float*)g.C + (int64_t)by * g.M * g.N;
-            if (row < g.M) {
-#pragma unroll
-              for (int b = 0; b < 4; ++b) {
-                const int64_t col = colb + 8 * b + 4 * lhalf;
-                if (col < g.N)
-                  *(float4*)(part + row * g.N + col) =
-                      make_float4(acc[i][j][4 * b], acc[i][j][4 * b + 1], acc[i][j][4 * b + 2], acc[i][j][4 * b + 3]);
-              }
-            }
-          }
-        }
-    } else if constexpr (Cfg::EPI == EPI_F32) {
+    if constexpr (Cfg::EPI == EPI_F32) {
       // 2:4 products, split-K partial rows (layout as below): 32 lanes store
       // 32 consecutive columns of one row per accumulator.
       float* part = (float*)g.C + (int64_t)by * g.M * g.N;
@@ -974,7 +929,8 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
     // outside them: their loads skip the bounds checks.
     auto steps_in_of = [&](int64_t m0, int64_t n0) __attribute__((always_inline)) {
       int r = 0;
-      if (m0 + BM <= g.m_valid && n0 + BN <= g.N) {
+      // (2:4 operand: rows past the end re-read the last one, see setup_a)
+      if ((SPARSE || m0 + BM <= g.m_valid) && n0 + BN <= g.N) {
         const int64_t k_in = (g.ka_valid < g.kb_valid ? g.ka_valid : g.kb_valid) - kbeg;
         r = k_in <= 0 ? 0 : (int)(k_in / BK < nsteps ? k_in / BK : nsteps);
       }
@@ -1100,6 +1056,13 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
       a_src(tm0, kbeg, second, v0, m0p);
       a_src(tm0, kbeg + BK, second, v1, m1p);
       (void)m1p;
+      if constexpr (SPARSE) {
+        const int rows = (int)(g.m_valid - tm0 < BM ? g.m_valid - tm0 : BM);
+#pragma unroll
+        for (int j = 0; j < LA; ++j) offA[j] = TA::lane_off(j, g.a_tiled ? 32 : g.lda, wave, lane, rows);
+#pragma unroll
+        for (int j = 0; j < LM; ++j) offM[j] = TMeta::lane_off(j, g.a_tiled ? 8 : g.ldam, wave, lane, rows);
+      }
       ca_p = (const char*)uniform_ptr(v0);
       ca_st = __builtin_amdgcn_readfirstlane((uint32_t)(v1 - v0));
       if constexpr (SPARSE) ca_m = (const char*)uniform_ptr(m0p);
