@@ -336,8 +336,8 @@ bool resident_down(int64_t T, int64_t r) { return resident_rank(r) && T > 2048; 
 // Workgroups per block of 128 tokens: the split of the nfb 64-feature blocks
 // with the fewest rounds of wave tiles (copying the tokens costs about 0.4 of
 // one).
-int resident_split(int64_t tiles, int64_t nfb, int64_t r) {
-  const int64_t nw = r == 512 ? 8 : 4, slots = device_cus() * (int64_t)(r == 512 ? 1 : 2);
+int resident_split(int64_t tiles, int64_t nfb, int64_t nw) {
+  const int64_t slots = device_cus() * (8 / nw);
   int best = 1;
   double best_cost = 1e30;
   for (int64_t s = 1; s <= nfb && s <= 16; ++s) {
@@ -349,15 +349,16 @@ int resident_split(int64_t tiles, int64_t nfb, int64_t r) {
 template <int EPI>
 hipError_t launch_resident(const char* tag, int64_t r, ResArgs g, hipStream_t st) {
   const int64_t tiles = cdiv(g.T, 128);
-  g.fsplit = resident_split(tiles, g.nfb, r);
+  const int nw = res_waves(EPI, (int)(r / 64));
+  g.fsplit = resident_split(tiles, g.nfb, nw);
   TimedLaunch tl(tag, st);
   const dim3 grid((unsigned)(tiles * g.fsplit));
   if (r == 128)
-    hipLaunchKernelGGL((resident_kernel<EPI, 2>), grid, dim3(256), 0, st, g);
+    hipLaunchKernelGGL((resident_kernel<EPI, 2>), grid, dim3(64 * nw), 0, st, g);
   else if (r == 256)
-    hipLaunchKernelGGL((resident_kernel<EPI, 4>), grid, dim3(256), 0, st, g);
+    hipLaunchKernelGGL((resident_kernel<EPI, 4>), grid, dim3(64 * nw), 0, st, g);
   else
-    hipLaunchKernelGGL((resident_kernel<EPI, 8>), grid, dim3(512), 0, st, g);
+    hipLaunchKernelGGL((resident_kernel<EPI, 8>), grid, dim3(64 * nw), 0, st, g);
   return hipGetLastError();
 }
 // C [T x M] = X W^T with W [M x r] in fragment order.

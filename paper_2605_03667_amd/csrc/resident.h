@@ -20,7 +20,7 @@
 // and 65536 tokens 302 against 323 us).
 //
 // Measured at 1B, 65536 tokens, against the 256 x 256 tiled kernel of gemm.h:
-// up projection with 2:4 selection 424 -> 307 us, masked dH 478 -> 340, Y
+// up projection with 2:4 selection 424 -> 307 us, masked dH 478 -> 334, Y
 // 149 -> 137, dx 158 -> 138; 350M: 145 -> 103, 175 -> 112, 53 -> 49, 56 -> 49.
 #pragma once
 
@@ -78,24 +78,40 @@ __device__ __forceinline__ void unroll8(F&& f) {
   f(std::integral_constant<int, 6>{}); f(std::integral_constant<int, 7>{});
 }
 
-// KP = K / 64 panels.  K = 512 fills the LDS, so one workgroup of eight waves
-// runs per CU; below, two workgroups of four.
+// The epilogues that need the stored activation of their tile.
+__host__ __device__ constexpr bool res_reads(int epi) { return epi == EPI_DH || epi == EPI_DH_DENSE; }
+// Waves of a workgroup.  K = 512 fills the LDS, so one workgroup of eight waves
+// runs per CU; below, two workgroups of four, but at K = 256 one of eight where the
+// epilogue reads: sharing the token block leaves 96 KB instead of 32 for what it reads.
+__host__ __device__ constexpr int res_waves(int epi, int kp) { return kp == 8 || (kp == 4 && res_reads(epi)) ? 8 : 4; }
+
+// KP = K / 64 panels.
 template <int EPI, int KP>
-__global__ __launch_bounds__(KP == 8 ? 512 : 256, 2) void resident_kernel(const ResArgs g) {
-  constexpr int NW = KP == 8 ? 8 : 4;
+__global__ __launch_bounds__(64 * res_waves(EPI, KP), 2) void resident_kernel(const ResArgs g) {
+  constexpr int NW = res_waves(EPI, KP);
   constexpr int PANEL = 128 * 128;   // bytes of one 64-wide panel of the token block
-  // READS: the epilogue needs the stored activation of its tile.  Each wave
-  // copies it by DMA to 4 KB of its own: SLOTS blocks of 16 tokens (SKB KB each),
-  // the first SLOTS at the tile's start, the others as slots come free, and for
-  // the compressed S the codes of all 128 tokens (1 KB).
-  constexpr bool READS = EPI == EPI_DH || EPI == EPI_DH_DENSE;
-  constexpr int SKB = EPI == EPI_DH ? 1 : 2, SLOTS = EPI == EPI_DH ? 3 : 2;
-  __shared__ __attribute__((aligned(1024))) char smem[KP * PANEL + (READS ? NW * 4096 : 0)];
+  // READS: each wave brings in the stored activation of its tile, 8 blocks of 16
+  // tokens (SKB KB each).  The first SLOTS are copied by DMA to LDS of its own at
+  // the tile's start (with the codes of all 128 tokens of a compressed S, 1 KB),
+  // the next REGS loaded to registers at the epilogue's start, where the fragments'
+  // are free (as many as there are without spills), and any left copied to slots that
+  // have come free.  An epilogue then waits for about one memory latency, not for one
+  // per 3 (dense: 2) blocks.  Microseconds before and after: dense dH at 350M, 32768
+  // tokens 131 / 123, at 1B, 16384 tokens 153 / 147; masked dH at 350M, 16381 tokens
+  // 42 / 39, at 1B, 65536 tokens 340 / 334.  (Cached instead of streaming reads: dense
+  // dH 120, but dP, which finds less of dH in the caches, 63 -> 71.)
+  constexpr bool READS = res_reads(EPI);
+  constexpr int SKB = EPI == EPI_DH ? 1 : 2, CODES = EPI == EPI_DH ? 1024 : 0;
+  constexpr int SLOTS = KP == 8 ? (EPI == EPI_DH ? 3 : 2) : (EPI == EPI_DH ? 8 : 6);
+  constexpr int REGS = KP == 8 ? (EPI == EPI_DH ? 3 : 4) : EPI == EPI_DH ? 0 : KP == 4 ? 1 : 2;
+  constexpr int AHEAD = SLOTS + REGS;
+  constexpr int SBUF = SLOTS * SKB * 1024 + CODES;
+  constexpr int LDS = KP * PANEL + (READS ? NW * SBUF : 0);
+  __shared__ __attribute__((aligned(1024))) char smem[LDS];
   // Waves take feature blocks from a counter (the two waves of a SIMD share it
   // unevenly, so a fixed deal ends ragged: k2 at 1B 313 against 297 us); where
-  // the tile's S fills the LDS to the last byte (of two workgroups at K = 256)
-  // they are dealt in turn.
-  constexpr bool COUNTER = !(READS && KP >= 4);
+  // the tile's S fills the LDS to the last byte they are dealt in turn.
+  constexpr bool COUNTER = LDS * (8 / NW) < 160 * 1024;
   __shared__ int s_next;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -171,18 +187,19 @@ __global__ __launch_bounds__(KP == 8 ? 512 : 256, 2) void resident_kernel(const 
   // Dense rows: after a permlane16 swap of the two row quarters of a pair,
   // lane group lg holds 8 consecutive features from 16 (lg % 2) + 8 (lg / 2) of
   // the pair's 32, so a store covers 64 bytes of each of 16 token rows.
-  char* sbuf = smem + KP * PANEL + wave * 4096;   // this wave's stored activation (READS)
+  char* sbuf = smem + KP * PANEL + wave * SBUF;   // this wave's stored activation (READS)
   const uint32_t sbuf_lds = lds_u32(sbuf);
   // Copies token block j of feature block fb, lane l's 16 bytes to slot byte
   // 16 l: the piece the epilogue's lane l reads.  (Rows past the last token and
   // features past the last re-read a valid piece; nothing uses them.)
+  // (j - AHEAD: the block whose slot a later copy takes)
   auto copy_s = [&](int fb, int j) __attribute__((always_inline)) {
     if constexpr (READS) {
       int le = lane;   // laundered: offsets formed here, not kept live
       asm volatile("" : "+v"(le));
       int row = j * 16 + (le & 15);
       row = row < t_end ? row : 0;
-      const uint32_t slot = sbuf_lds + (j % SLOTS) * SKB * 1024;
+      const uint32_t slot = sbuf_lds + (j < SLOTS ? j : j - AHEAD) * SKB * 1024;
       if constexpr (EPI == EPI_DH) {
         const int64_t tb = n0 & ~(int64_t)255;
         const int64_t R = g.T - tb < 256 ? g.T - tb : 256;
@@ -208,22 +225,47 @@ __global__ __launch_bounds__(KP == 8 ? 512 : 256, 2) void resident_kernel(const 
         int row = h * 32 + (le >> 1);
         row = row < t_end ? row : 0;
         dma_b32_nt_s(g.sm + tb * g.ldm + (int64_t)fb * R * 8 + (n0 - tb) * 8, (uint32_t)(row * 8 + (le & 1) * 4),
-                     sbuf_lds + SLOTS * 1024 + h * 256);
+                     sbuf_lds + SLOTS * SKB * 1024 + h * 256);
       }
+    }
+  };
+  // The REGS blocks after those, the same pieces to registers.
+  u32x4 sreg[REGS > 0 ? REGS * SKB : 1];
+  auto load_s = [&](int fb, int le) __attribute__((always_inline)) {
+    if constexpr (READS) {
+#pragma unroll
+      for (int k = 0; k < REGS; ++k) {
+        int row = (SLOTS + k) * 16 + (le & 15);
+        row = row < t_end ? row : 0;
+        if constexpr (EPI == EPI_DH) {
+          const int64_t tb = n0 & ~(int64_t)255;
+          const int64_t R = g.T - tb < 256 ? g.T - tb : 256;
+          const char* p = (const char*)uniform_ptr(g.sv + tb * g.ldv + (int64_t)fb * R * 32 + (n0 - tb) * 32);
+          sreg[k] = __builtin_nontemporal_load((const gu32x4*)(p + (uint32_t)(row * 64 + (le >> 4) * 16)));
+        } else {
+          const int f = 16 * ((le >> 4) & 1) + 8 * (le >> 5), left = g.f_valid - fb * 64;
+          const char* p = (const char*)uniform_ptr(g.act + n0 * g.ldc + fb * 64);
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            sreg[2 * k + h] = __builtin_nontemporal_load(
+                (const gu32x4*)(p + (uint32_t)((uint32_t)row * (uint32_t)(g.ldc * 2) + (f + 32 * h < left ? f + 32 * h : 0) * 2)));
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
   // Waits for the copy of token block j.  The first SLOTS are older than the
   // weight loads of the last panel (8 of them follow).  Later ones follow the
-  // stores of block j - SLOTS; after them come SLOTS - 1 blocks' stores and the
+  // stores of block j - AHEAD; after them come AHEAD - 1 blocks' stores and the
   // copies of the blocks below 8 among those.  Where a store may have been
   // skipped (ragged tiles) everything is waited for.
   auto wait_s = [&](auto jc, bool full) __attribute__((always_inline)) {
     constexpr int j = decltype(jc)::value;
     if constexpr (j == 0) {
       wait_vmcnt<8>();
-    } else if constexpr (j >= SLOTS) {
-      constexpr int copies = 7 - j < SLOTS - 1 ? 7 - j : SLOTS - 1;
-      if (full) wait_vmcnt<SKB * (SLOTS - 1 + copies)>();
+    } else if constexpr (j >= AHEAD) {
+      constexpr int copies = 7 - j < AHEAD - 1 ? 7 - j : AHEAD - 1;
+      if (full) wait_vmcnt<SKB * (AHEAD - 1 + copies)>();
       else wait_vmcnt<0>();
     }
   };
@@ -300,10 +342,13 @@ __global__ __launch_bounds__(KP == 8 ? 512 : 256, 2) void resident_kernel(const 
       char* dv = (char*)uniform_ptr(g.dv + tb * g.ldv + (int64_t)cur * R * 32 + (n0 - tb) * 32);
       const char* sl = sbuf + le * 16;
       const char* sc = sbuf + SLOTS * 1024 + e16 * 8;
+      wait_s(std::integral_constant<int, 0>{}, true);
+      load_s(cur, le);
       unroll8([&](auto jc) __attribute__((always_inline)) {
         constexpr int j = decltype(jc)::value;
-        wait_s(jc, t_end == 128);
-        const u32x4 sv = *(const u32x4*)(sl + (j % SLOTS) * 1024);
+        if constexpr (j > 0) wait_s(jc, t_end == 128);
+        const u32x4 sv = j >= SLOTS && j < AHEAD ? sreg[j >= SLOTS && j < AHEAD ? j - SLOTS : 0]
+                                                 : *(const u32x4*)(sl + (j < SLOTS ? j : j - AHEAD) * 1024);
         const u32x2 m = *(const u32x2*)(sc + j * 128);
         uint32_t v[4] = {sv[0], sv[1], sv[2], sv[3]};
         // a subnormal s, which the raw square root flushes (bit pattern v in
@@ -341,21 +386,28 @@ __global__ __launch_bounds__(KP == 8 ? 512 : 256, 2) void resident_kernel(const 
         }
         transpose4(v);
         if (j * 16 + e16 < t_end) *(gu32x4*)(dv + j * 1024 + (uint32_t)(e16 * 64 + eg * 16)) = u32x4{v[0], v[1], v[2], v[3]};
-        if constexpr (j + SLOTS < 8) copy_s(cur, j + SLOTS);
+        if constexpr (j + AHEAD < 8) copy_s(cur, j + AHEAD);
         __builtin_amdgcn_sched_barrier(0);
       });
     }
     if constexpr (EPI == EPI_BF16 || EPI == EPI_ACT_DENSE || EPI == EPI_DH_DENSE) {
       const int f = cur * 64 + 16 * (eg & 1) + 8 * (eg >> 1);
+      if constexpr (READS) {
+        wait_s(std::integral_constant<int, 0>{}, true);
+        load_s(cur, le);
+      }
       unroll8([&](auto jc) __attribute__((always_inline)) {
         constexpr int j = decltype(jc)::value;
         uint16_t* dst = g.C + (n0 + j * 16 + e16) * g.ldc + f;
         const bool ok = j * 16 + e16 < t_end;
         u32x4 sin[2];
         if constexpr (EPI == EPI_DH_DENSE) {
-          wait_s(jc, t_end == 128 && cur * 64 + 64 <= g.f_valid);
+          if constexpr (j > 0) wait_s(jc, t_end == 128 && cur * 64 + 64 <= g.f_valid);
 #pragma unroll
-          for (int h = 0; h < 2; ++h) sin[h] = *(const u32x4*)(sbuf + ((j % SLOTS) * 2 + h) * 1024 + le * 16);
+          for (int h = 0; h < 2; ++h) {
+            if constexpr (j >= SLOTS && j < AHEAD) sin[h] = sreg[2 * (j - SLOTS) + h];
+            else sin[h] = *(const u32x4*)(sbuf + ((j < SLOTS ? j : j - AHEAD) * 2 + h) * 1024 + le * 16);
+          }
         }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -411,7 +463,7 @@ __global__ __launch_bounds__(KP == 8 ? 512 : 256, 2) void resident_kernel(const 
           const auto y = __builtin_amdgcn_permlane16_swap(m[0][1], m[1][1], false, false);
           if (ok && f + 32 * h < g.f_valid) *(u32x4*)(dst + 32 * h) = u32x4{x[0], y[0], x[1], y[1]};
         }
-        if constexpr (READS && j + SLOTS < 8) copy_s(cur, j + SLOTS);
+        if constexpr (READS && j + AHEAD < 8) copy_s(cur, j + AHEAD);
         __builtin_amdgcn_sched_barrier(0);
       });
     }
