@@ -216,10 +216,12 @@ hipError_t launch(const char* tag, GemmArgs g, int splits, hipStream_t st) {
 // Dense products (plain.h): 256 x 256 tiles on 8 waves with the streaming operand
 // three steps deep, 256 x 128 for narrow outputs; 128 x 128 on 4 waves, two
 // workgroups per CU.
-using PlainNT = PlainCfg<256, 256, 4, 2, false, 3, 2>;
-using PlainNTn = PlainCfg<256, 128, 4, 2, false, 3, 3>;
-template <bool F32>
-using PlainNTs = PlainCfg<128, 128, 2, 2, F32, 3, 2>;
+template <int EPI>
+using PlainNT = PlainCfg<256, 256, 4, 2, EPI, 3, 2>;
+template <int EPI>
+using PlainNTn = PlainCfg<256, 128, 4, 2, EPI, 3, 3>;
+template <int EPI>
+using PlainNTs = PlainCfg<128, 128, 2, 2, EPI, 3, 2>;
 
 template <class Cfg>
 hipError_t launch_plain(const char* tag, GemmArgs g, int splits, hipStream_t st) {
@@ -313,7 +315,7 @@ hipError_t launch_staged(const char* tag, GemmArgs g, hipStream_t st) {
   if (tiles_m % 2 == 0 && tiles_m * 256 * g.K * 2 > (int64_t(3) << 20)) g.m_groups = 2;
   return launch<CfgNT<256, EPI, true>>(tag, g, 1, st);
 }
-// Epilogues that write or read the dense activation (features along M).
+// Epilogues that write the dense dH (features along M).
 template <int EPI>
 hipError_t launch_act(const char* tag, const GemmArgs& g, hipStream_t st) {
   if (few_tiles(g.M, g.N, 256, 256)) return launch<CfgNTs<EPI, true>>(tag, g, 1, st);
@@ -457,11 +459,12 @@ Route route_down(int64_t T, int64_t d, int64_t r) {
   return resident_down(T, r) ? RESIDENT : TILED;
 }
 
-// Dense product C[M x N] = A[M x K] * Bt[N x K]^T in bf16 (`part`: split-K
-// partials for small problems, may be null).
+// Dense product C[M x N] = A[M x K] * Bt[N x K]^T in bf16, or relu(.)^2 of it
+// (`part`: split-K partials for small problems of EPI_BF16, may be null).
 // b_nsk > 0: Bt is blocked (blocked_index, b_nsk K blocks per panel; ldb is
 // then ignored).
-hipError_t gemm_nt_bf16(const char* tag, const uint16_t* A, int64_t lda, const uint16_t* Bt, int64_t ldb, uint16_t* C, int64_t ldc,
+template <int EPI>
+hipError_t gemm_nt(const char* tag, const uint16_t* A, int64_t lda, const uint16_t* Bt, int64_t ldb, uint16_t* C, int64_t ldc,
                         int64_t M, int64_t N, int64_t K, hipStream_t st, float* part = nullptr, int64_t b_nsk = 0) {
   GemmArgs g{};
   g.A = A; g.lda = lda; g.B = Bt; g.ldb = b_nsk > 0 ? 64 : ldb; g.b_nsk = b_nsk; g.C = C; g.ldc = ldc;
@@ -472,15 +475,18 @@ hipError_t gemm_nt_bf16(const char* tag, const uint16_t* A, int64_t lda, const u
       g.C = part;
       g.ldc = N;
       g.k_split = p.k_split;
-      
-      const hipError_t e = launch_plain<PlainNTs<true>>(tag, g, p.splits, st);
+      const hipError_t e = launch_plain<PlainNTs<EPI_F32>>(tag, g, p.splits, st);
       if (e != hipSuccess) return e;
       return reduce_bf16(part, p.splits, M, N, C, ldc, st);
     }
-    return launch_plain<PlainNTs<false>>(tag, g, 1, st);
+    return launch_plain<PlainNTs<EPI>>(tag, g, 1, st);
   }
-  if (N <= 128) return launch_plain<PlainNTn>(tag, g, 1, st);
-  return launch_plain<PlainNT>(tag, g, 1, st);
+  if (N <= 128) return launch_plain<PlainNTn<EPI>>(tag, g, 1, st);
+  return launch_plain<PlainNT<EPI>>(tag, g, 1, st);
+}
+hipError_t gemm_nt_bf16(const char* tag, const uint16_t* A, int64_t lda, const uint16_t* Bt, int64_t ldb, uint16_t* C, int64_t ldc,
+                        int64_t M, int64_t N, int64_t K, hipStream_t st, float* part = nullptr, int64_t b_nsk = 0) {
+  return gemm_nt<EPI_BF16>(tag, A, lda, Bt, ldb, C, ldc, M, N, K, st, part, b_nsk);
 }
 
 // Weight gradients (wgrad.h): the jobs of one backward and how their (tile, step)
@@ -738,11 +744,7 @@ hipError_t run_fwd(const FfnArgs& a, hipStream_t st) {
     if (up == RESIDENT) {
       ELAS_TRY(launch_resident<EPI_ACT_DENSE>(tag, r, q, st));
     } else {
-      GemmArgs g{};
-      g.A = V_upT; g.lda = r; g.B = a.P; g.ldb = r;
-      g.M = Fp; g.N = T; g.K = r; g.m_valid = F_rows; g.ka_valid = r; g.kb_valid = r;
-      g.act = a.s_vals; g.ld_act = F; g.f_valid = F; g.act_square = 1;
-      ELAS_TRY(launch_act<EPI_ACT_DENSE>(tag, g, st));
+      ELAS_TRY(gemm_nt<EPI_ACT_DENSE>(tag, a.P, r, V_upT, r, a.s_vals, F, T, F, r, st));
     }
     if (route_long(T, r) == SMALL)
       ELAS_TRY(launch_small_long<false>("k3_down_gemm_dense", small_dense(U_downT, ld_ud, r, F, a.s_vals, F, T, a.Z), st));
@@ -759,16 +761,11 @@ hipError_t run_fwd(const FfnArgs& a, hipStream_t st) {
 // Full-rank ReLU^2 FFN forward (the comparison of Table 3, Sec. 4.2.3).  The
 // weights come in the orientation of Eq. 1 (W_up [F x d], W_down [d x F]),
 // which is already the K-contiguous operand layout, so nothing is re-laid out:
-// S = relu(x W_up^T)^2 through the fused dense-activation epilogue of the
-// dense-mode up projection, then Y = S W_down^T.
+// S = relu(x W_up^T)^2 with the activation in the product's epilogue, then
+// Y = S W_down^T.
 hipError_t run_fullrank_fwd(const uint16_t* x, const uint16_t* W_up, const uint16_t* W_down, int64_t T,
                             int64_t d, int64_t F, uint16_t* y, uint16_t* S, hipStream_t st) {
-  // S^T = relu(W_up x^T)^2, written token-major [T x F]
-  GemmArgs g{};
-  g.A = W_up; g.lda = d; g.B = x; g.ldb = d;
-  g.M = F; g.N = T; g.K = d; g.m_valid = F; g.ka_valid = d; g.kb_valid = d;
-  g.act = S; g.ld_act = F; g.f_valid = F; g.act_square = 1;
-  ELAS_TRY(launch_act<EPI_ACT_DENSE>("fr_up_relu2", g, st));
+  ELAS_TRY(gemm_nt<EPI_ACT_DENSE>("fr_up_relu2", x, d, W_up, d, S, F, T, F, d, st));
   // Y = S W_down^T
   ELAS_TRY(gemm_nt_bf16("fr_down_gemm", S, F, W_down, F, y, d, T, d, F, st));
   return hipSuccess;
@@ -859,7 +856,7 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
       q.C = w.dH; q.act = a.s_vals; q.ldc = F; q.f_valid = (int)F;
       ELAS_TRY(launch_resident<EPI_DH_DENSE>("b3_dH_dense", r, q, st));
     } else {
-      g.act = const_cast<uint16_t*>(a.s_vals); g.act_square = 1;
+      g.act = a.s_vals;
       ELAS_TRY(launch_act<EPI_DH_DENSE>("b3_dH_dense", g, st));
     }
     // dP = dH V_up^T (dense)

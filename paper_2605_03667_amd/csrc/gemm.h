@@ -49,7 +49,7 @@ enum EpiMode {
   EPI_F32 = 1,        // fp32 split-K partials (here: 2:4 products)
   EPI_SPARSIFY = 2,   // ReLU^2 + top-2 of 4 + compressed write (C = H^T)
   EPI_DH = 3,         // dH = dS * mask * 2 relu(h), compressed (C = dS^T)
-  EPI_ACT_DENSE = 4,  // dense activation: relu(h)^2 (act_square) or relu(h) (C = H^T)
+  EPI_ACT_DENSE = 4,  // dense activation relu(h)^2 (not here)
   EPI_DH_DENSE = 5,   // dense dH = dS * 2 r, r from a dense activation (C = dS^T)
   EPI_DH_STE = 6,     // dense dH = dS * 2 relu(h), h = A B^T of the first operand pair (C = dS^T)
 };
@@ -82,13 +82,12 @@ struct GemmArgs {
   uint8_t* sm;         // metadata of S (N rows, pitch ldm)
   int64_t ldv, ldm;
   uint16_t* dv;        // EPI_DH: kept values of dH (N rows, pitch ldv), written
-  // EPI_ACT_DENSE / EPI_DH_DENSE: dense [N x ld_act] activations (tokens as
+  // EPI_DH_DENSE / EPI_DH_STE: dense [N x ld_act] activations (tokens as
   // rows), features f < f_valid only.
-  uint16_t* act;       // ACT_DENSE: written; DH_DENSE: read (r = bf16(sqrt(a)) if act_square, else a)
-  uint16_t* dact;      // DH_DENSE: dense dH, written (pitch ld_act)
+  const uint16_t* act; // DH_DENSE: s = relu(h)^2, read
+  uint16_t* dact;      // dense dH, written (pitch ld_act)
   int64_t ld_act;
   int64_t f_valid;
-  int act_square;
   int tiles_m, tiles_n;
   // M-fast direct kernels: when > 1, the XCDs split the M tiles into this many
   // contiguous panels (XCD x takes panel x % m_groups and a share of the N
@@ -628,7 +627,7 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
             if (inside || (row + dr < g.M && col < g.N)) base[dr * g.ldc] = (__bf16)acc[i][j][e];
           }
         }
-    } else if constexpr (Cfg::EPI == EPI_ACT_DENSE || Cfg::EPI == EPI_DH_DENSE || Cfg::EPI == EPI_DH_STE) {
+    } else if constexpr (Cfg::EPI == EPI_DH_DENSE || Cfg::EPI == EPI_DH_STE) {
       // C rows are features f, columns tokens t: accumulators 4b..4b+3 of a
       // lane are features 8b + 4h + 0..3 of token column l % 32.  Lanes l and
       // l+32 exchange halves so that each writes 16 contiguous features
@@ -644,24 +643,7 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
           const int64_t t = n0 + wn * TN + j * 32 + lr;
           const int64_t f32 = m0 + wm * TM + i * 32;
           uint2 mine[4];   // block b: features f32 + 8b + 4h .. +3 as 4 bf16
-          if constexpr (Cfg::EPI == EPI_ACT_DENSE) {
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-              uint32_t v[2];
-#pragma unroll
-              for (int e = 0; e < 2; ++e) {
-                // h relu'd and rounded to bf16 (RNE), squared (act_square) and rounded
-                const uint32_t r = bf16x2_rne(relu_f32(acc[i][j][4 * b + 2 * e]), relu_f32(acc[i][j][4 * b + 2 * e + 1]));
-                if (g.act_square) {
-                  const float lo = __builtin_bit_cast(float, r << 16), hi = __builtin_bit_cast(float, r & 0xFFFF0000u);
-                  v[e] = bf16x2_rne(lo * lo, hi * hi);
-                } else {
-                  v[e] = r;
-                }
-              }
-              mine[b] = make_uint2(v[0], v[1]);
-            }
-          } else if constexpr (Cfg::EPI == EPI_DH_STE) {
+          if constexpr (Cfg::EPI == EPI_DH_STE) {
             // relu(h) from the stash: accumulator 4b + q of the h product is
             // feature 8b + 4h + q, as for dS
 #pragma unroll
@@ -695,28 +677,27 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
               }
             }
             const bool tiny = (vmin[0] < vmin[1] ? vmin[0] : vmin[1]) < 0x7Fu;
-            if (g.act_square) {   // r = bf16(sqrt(s)) recovers relu(h) exactly
-              float rt[4][4];
-              if (__builtin_amdgcn_ballot_w64(tiny) == 0) {
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-#pragma unroll
-                  for (int q = 0; q < 4; ++q) rt[b][q] = __builtin_amdgcn_sqrtf(x[b][q]);
-              } else {
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-#pragma unroll
-                  for (int q = 0; q < 4; ++q) rt[b][q] = sqrt_for_bf16(x[b][q]);
-              }
+            // r = bf16(sqrt(s)) recovers relu(h) exactly
+            float rt[4][4];
+            if (__builtin_amdgcn_ballot_w64(tiny) == 0) {
 #pragma unroll
               for (int b = 0; b < 4; ++b)
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                  const uint32_t rr = bf16x2_rne(rt[b][2 * e], rt[b][2 * e + 1]);
-                  x[b][2 * e] = __builtin_bit_cast(float, rr << 16);
-                  x[b][2 * e + 1] = __builtin_bit_cast(float, rr & 0xFFFF0000u);
-                }
+                for (int q = 0; q < 4; ++q) rt[b][q] = __builtin_amdgcn_sqrtf(x[b][q]);
+            } else {
+#pragma unroll
+              for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) rt[b][q] = sqrt_for_bf16(x[b][q]);
             }
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+              for (int e = 0; e < 2; ++e) {
+                const uint32_t rr = bf16x2_rne(rt[b][2 * e], rt[b][2 * e + 1]);
+                x[b][2 * e] = __builtin_bit_cast(float, rr << 16);
+                x[b][2 * e + 1] = __builtin_bit_cast(float, rr & 0xFFFF0000u);
+              }
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
               uint32_t v[2];
@@ -744,7 +725,7 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
           }
           const int64_t f = f32 + 16 * lh;
           if (t < g.N) {
-            uint16_t* dst = (Cfg::EPI == EPI_ACT_DENSE ? g.act : g.dact) + t * g.ld_act + f;
+            uint16_t* dst = g.dact + t * g.ld_act + f;
             if (f + 8 <= g.f_valid) *(uint4*)dst = make_uint4(lo[0], lo[1], lo[2], lo[3]);
             if (f + 16 <= g.f_valid) *(uint4*)(dst + 8) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
           }
@@ -1023,9 +1004,9 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
     // a pointer add.  Eight waves run their scalar code on the CU's one
     // scalar unit, so the per-step scalar instruction count is what bounds
     // the copy issue.  The two-pair kernel sets its cursors up again at the
-    // second pair's step 0.  (The dense-activation epilogues keep the general
-    // path: with the cursors they measured no faster.)
-    constexpr bool LEAN = Cfg::EPI != EPI_ACT_DENSE && Cfg::EPI != EPI_DH_DENSE;
+    // second pair's step 0.  (The dense dH epilogue keeps the general path:
+    // with the cursors it measured no faster.)
+    constexpr bool LEAN = Cfg::EPI != EPI_DH_DENSE;
     // A 2:4 operand's metadata advances by 1/8 of its kept values' stride
     // (tiled: 8 R against 64 R bytes; rows: BK/8 against BK bytes).  A stride
     // is at most BK rows of a pitch the entry points bound by 65536 elements

@@ -17,7 +17,10 @@
 // workgroup per CU, checked copies on ragged tiles; microseconds): 350M shapes, k1 at
 // 16381 tokens 25.5 -> 18.5, at 33333 54 -> 35; dense Z at 32768 tokens 88 -> 70, dP
 // 80 -> 58; 130M full-rank down product at 8192 tokens 44 -> 33; 1B at 65536 tokens
-// 127 -> 130, within what the rest of the step gains from the power left.
+// 127 -> 130, within what the rest of the step gains from the power left.  Full-rank
+// up products with their ReLU^2, which that loop computed transposed, against this
+// (with the timing events' few): 60M at 700 tokens 16 -> 13, 350M at 4099 48 -> 33,
+// 1B at 2048 79 -> 56 and at 16384 394 -> 351.
 #pragma once
 
 #include "gemm.h"
@@ -25,10 +28,11 @@
 namespace elas {
 
 // SA, SB: stages of A's and of B's ring.
-template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, bool F32_, int SA_, int SB_>
+// EPI: EPI_BF16, EPI_F32 (split-K partials) or EPI_ACT_DENSE (relu(.)^2 in bf16).
+template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, int EPI_, int SA_, int SB_>
 struct PlainCfg {
   static constexpr int BM = BM_, BN = BN_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, SA = SA_, SB = SB_;
-  static constexpr bool F32 = F32_;
+  static constexpr int EPI = EPI_;
   static constexpr int NW = WAVES_M_ * WAVES_N_, NT = 64 * NW, BK = 64;
   static constexpr int TM = BM_ / WAVES_M_, TN = BN_ / WAVES_N_;
   static constexpr int AB = BM_ * 128, BB = BN_ * 128;   // bytes of a stage
@@ -228,16 +232,26 @@ __global__ __launch_bounds__(Cfg::NT, 2) void plain_kernel(const GemmArgs g) {
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
       const int64_t row = m0 + wm * TM + i * 16 + l16;
-      if constexpr (!Cfg::F32) {
+      if constexpr (Cfg::EPI != EPI_F32) {
+        auto out = [&](float x, float y) __attribute__((always_inline)) {
+          if constexpr (Cfg::EPI == EPI_ACT_DENSE) {
+            // h relu'd and rounded to bf16, squared and rounded
+            const uint32_t r = bf16x2_rne(relu_f32(x), relu_f32(y));
+            const float lo = __builtin_bit_cast(float, r << 16), hi = __builtin_bit_cast(float, r & 0xFFFF0000u);
+            return bf16x2_rne(lo * lo, hi * hi);
+          } else {
+            return bf16x2_rne(x, y);
+          }
+        };
         // after a permlane16 swap of two neighbouring blocks lane group lg holds 8
         // consecutive columns from 16 (lg % 2) + 8 (lg / 2) of their 32
 #pragma unroll
         for (int j = 0; j < FN; j += 2) {
           const int64_t col = n0 + wn * TN + j * 16 + 16 * (lg & 1) + 8 * (lg >> 1);
-          const auto x = __builtin_amdgcn_permlane16_swap(bf16x2_rne(acc[i][j][0], acc[i][j][1]),
-                                                          bf16x2_rne(acc[i][j + 1][0], acc[i][j + 1][1]), false, false);
-          const auto y = __builtin_amdgcn_permlane16_swap(bf16x2_rne(acc[i][j][2], acc[i][j][3]),
-                                                          bf16x2_rne(acc[i][j + 1][2], acc[i][j + 1][3]), false, false);
+          const auto x = __builtin_amdgcn_permlane16_swap(out(acc[i][j][0], acc[i][j][1]),
+                                                          out(acc[i][j + 1][0], acc[i][j + 1][1]), false, false);
+          const auto y = __builtin_amdgcn_permlane16_swap(out(acc[i][j][2], acc[i][j][3]),
+                                                          out(acc[i][j + 1][2], acc[i][j + 1][3]), false, false);
           if (row < g.M && col < g.N) *(uint4*)((__bf16*)g.C + row * g.ldc + col) = make_uint4(x[0], y[0], x[1], y[1]);
         }
       } else {
