@@ -593,7 +593,7 @@ WgradPlan wgrad_plan(const FfnArgs& a, const BwdWs& w, bool dense, bool ste) {
   p.add(a.Z, r, nullptr, 0, a.dy, r, d, a.dV_down, r, false);
   if (dense) p.add(a.s_vals, F, nullptr, 0, w.dZ, F, r, a.dU_down, F, false);
   else p.add(a.s_vals, ldv, sm, ldm, w.dZ, Fp, r, a.dU_down, F, false);
-  if (dense || ste) p.add(w.dH, F, nullptr, 0, a.P_in, F, r, a.dV_up, F, true);
+  if (dense || ste) p.add(w.dH, Fp, nullptr, 0, a.P_in, F, r, a.dV_up, F, true);
   else p.add(w.dH, ldv, sm, ldm, a.P_in, Fp, r, a.dV_up, F, true);
   p.add(a.x, d, nullptr, 0, w.dP, d, r, a.dU_up, d, false);
   p.finish(T);
@@ -601,14 +601,18 @@ WgradPlan wgrad_plan(const FfnArgs& a, const BwdWs& w, bool dense, bool ste) {
   return p;
 }
 // dH is compressed [T x ldv] in the sparse backward and dense [T x F] in the
-// dense and straight-through ones; the straight-through backward also holds
-// V_up^T (relu(h) is recomputed tile by tile inside the dH kernel).
+// dense and straight-through ones, at a pitch of whole cache lines (at d_ff = 2736 or
+// 5464 a 64-feature piece of a row of F would straddle two; us, pitch F against Fp:
+// 350M dense, 32768 tokens, dH 123 / 118, dP 62.5 / 59; 1B dense, 16384, 147 / 139,
+// 105 / 94, weight gradients 244 / 231; straight-through 1B, 32768, 401 / 386, 169 /
+// 165, 519 / 492).  The straight-through backward also holds V_up^T (relu(h) is
+// recomputed tile by tile inside the dH kernel).
 BwdWs bwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ste) {
   const int64_t Fp = pad64(F);
   Carver c{p};
   BwdWs w{};
   w.dZ = c.take<uint16_t>(T * r);
-  w.dH = c.take<uint16_t>(T * ((dense || ste) ? F : vals_ld(F)));
+  w.dH = c.take<uint16_t>(T * ((dense || ste) ? Fp : vals_ld(F)));
   w.dP = c.take<uint16_t>(T * r);
   if (ste) w.V_upT = c.take<uint16_t>(Fp * r);
   w.V_upB = c.take<uint16_t>(pad256(r) * Fp);
@@ -845,7 +849,7 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
     GemmArgs g{};
     g.A = a.U_down; g.lda = r; g.B = w.dZ; g.ldb = r;
     g.M = Fp; g.N = T; g.K = r; g.m_valid = F; g.ka_valid = r; g.kb_valid = r;
-    g.ld_act = F; g.f_valid = F; g.dact = w.dH;
+    g.ld_act = F; g.ld_dact = Fp; g.f_valid = F; g.dact = w.dH;
     if (a.ste) {
       // one kernel per tile: h^T = V_up^T P^T over the first r contraction
       // steps (V_up^T rows >= F read as zero), relu(h) kept in registers, then
@@ -853,7 +857,7 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
       g.A = w.V_upT; g.B = a.P_in; g.A2 = a.U_down; g.B2 = w.dZ;
       ELAS_TRY(launch_act<EPI_DH_STE>("b3_dH_ste", g, st));
     } else if (wide == RESIDENT) {
-      q.C = w.dH; q.act = a.s_vals; q.ldc = F; q.f_valid = (int)F;
+      q.C = w.dH; q.ldc = Fp; q.act = a.s_vals; q.ld_act = F; q.f_valid = (int)F;
       ELAS_TRY(launch_resident<EPI_DH_DENSE>("b3_dH_dense", r, q, st));
     } else {
       g.act = a.s_vals;
@@ -861,9 +865,9 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
     }
     // dP = dH V_up^T (dense)
     if (lng == SMALL)
-      ELAS_TRY(launch_small_long<false>("b5_dP_dense", small_dense(a.V_up, F, r, F, w.dH, F, T, w.dP), st));
+      ELAS_TRY(launch_small_long<false>("b5_dP_dense", small_dense(a.V_up, F, r, F, w.dH, Fp, T, w.dP), st));
     else
-      ELAS_TRY(gemm_nt_bf16("b5_dP_dense", w.dH, F, w.V_upB, F, w.dP, r, T, r, F, st, w.part, nsk_vu));
+      ELAS_TRY(gemm_nt_bf16("b5_dP_dense", w.dH, Fp, w.V_upB, F, w.dP, r, T, r, F, st, w.part, nsk_vu));
   }
   // the four weight gradients
   ELAS_TRY(wgrad_plan(a, w, a.dense, a.ste).launch(a.dense ? "b2467_weight_grads_dense" : a.ste ? "b2467_weight_grads_ste"

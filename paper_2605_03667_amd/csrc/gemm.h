@@ -82,11 +82,11 @@ struct GemmArgs {
   uint8_t* sm;         // metadata of S (N rows, pitch ldm)
   int64_t ldv, ldm;
   uint16_t* dv;        // EPI_DH: kept values of dH (N rows, pitch ldv), written
-  // EPI_DH_DENSE / EPI_DH_STE: dense [N x ld_act] activations (tokens as
-  // rows), features f < f_valid only.
+  // EPI_DH_DENSE / EPI_DH_STE: dense tensors of N token rows, features f <
+  // f_valid only.
   const uint16_t* act; // DH_DENSE: s = relu(h)^2, read
-  uint16_t* dact;      // dense dH, written (pitch ld_act)
-  int64_t ld_act;
+  uint16_t* dact;      // dense dH, written
+  int64_t ld_act, ld_dact;
   int64_t f_valid;
   int tiles_m, tiles_n;
   // M-fast direct kernels: when > 1, the XCDs split the M tiles into this many
@@ -725,7 +725,7 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
           }
           const int64_t f = f32 + 16 * lh;
           if (t < g.N) {
-            uint16_t* dst = g.dact + t * g.ld_act + f;
+            uint16_t* dst = g.dact + t * g.ld_dact + f;
             if (f + 8 <= g.f_valid) *(uint4*)dst = make_uint4(lo[0], lo[1], lo[2], lo[3]);
             if (f + 16 <= g.f_valid) *(uint4*)(dst + 8) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
           }

@@ -55,10 +55,10 @@ struct ResArgs {
   uint16_t* dv;        // EPI_DH: kept values of dH, tiled
   // Dense output [T x features], features < f_valid (a multiple of 8):
   // EPI_BF16 the product, EPI_ACT_DENSE relu(.)^2, EPI_DH_DENSE the product
-  // times 2 relu(h) with s = relu(h)^2 read from act (same shape and pitch).
+  // times 2 relu(h) with s = relu(h)^2 read from act (same shape).
   uint16_t* C;
   const uint16_t* act;
-  int64_t ldc;
+  int64_t ldc, ld_act;
   int f_valid;
 };
 
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(64 * res_waves(EPI, KP), 2) void resident_kernel(co
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const int fh = f + 32 * h < left ? f + 32 * h : 0;
-          dma_b128_nt_s(g.act + n0 * g.ldc + fb * 64, (uint32_t)row * (uint32_t)(g.ldc * 2) + fh * 2, slot + h * 1024);
+          dma_b128_nt_s(g.act + n0 * g.ld_act + fb * 64, (uint32_t)row * (uint32_t)(g.ld_act * 2) + fh * 2, slot + h * 1024);
         }
       }
     }
@@ -244,11 +244,11 @@ __global__ __launch_bounds__(64 * res_waves(EPI, KP), 2) void resident_kernel(co
           sreg[k] = __builtin_nontemporal_load((const gu32x4*)(p + (uint32_t)(row * 64 + (le >> 4) * 16)));
         } else {
           const int f = 16 * ((le >> 4) & 1) + 8 * (le >> 5), left = g.f_valid - fb * 64;
-          const char* p = (const char*)uniform_ptr(g.act + n0 * g.ldc + fb * 64);
+          const char* p = (const char*)uniform_ptr(g.act + n0 * g.ld_act + fb * 64);
 #pragma unroll
           for (int h = 0; h < 2; ++h)
             sreg[2 * k + h] = __builtin_nontemporal_load(
-                (const gu32x4*)(p + (uint32_t)((uint32_t)row * (uint32_t)(g.ldc * 2) + (f + 32 * h < left ? f + 32 * h : 0) * 2)));
+                (const gu32x4*)(p + (uint32_t)((uint32_t)row * (uint32_t)(g.ld_act * 2) + (f + 32 * h < left ? f + 32 * h : 0) * 2)));
         }
       }
       __builtin_amdgcn_sched_barrier(0);
