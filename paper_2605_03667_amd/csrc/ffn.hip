@@ -243,6 +243,9 @@ hipError_t launch_plain(const char* tag, GemmArgs g, int splits, hipStream_t st)
 // many (twice as many for the staged 2:4 epilogues, which need 256 features).
 // In between: 256 x 128 tiles on 8 waves (64 x 64 per wave), four stages (136 KB).
 using CfgSPn = GemmCfg<256, 128, 4, 2, OP_SP, OP_K, EPI_BF16, false, 4, true, false, 64>;
+// Row-layout operands (elas_spmm_24): 128 K per step in two stages (136 KB), so that a
+// row's kept values come 128 bytes at a time, a cache line, and not 64.
+using CfgSPr = GemmCfg<256, 128, 4, 2, OP_SP, OP_K, EPI_BF16, false, 2, true, false, 128>;
 using CfgSPs = GemmCfg<128, 128, 2, 2, OP_SP, OP_K, EPI_BF16, false, 3, true, false, 64>;
 
 bool few_tiles(int64_t M, int64_t N, int bm, int bn) { return cdiv(M, bm) * cdiv(N, bn) * 4 < 3LL * device_cus(); }
@@ -297,12 +300,15 @@ hipError_t launch_sp(const char* tag, GemmArgs g, hipStream_t st, float* part = 
   }
   // Microseconds per K step of one round of tiles (measured at 86 steps: 256 x 256
   // 215 us in two rounds, 256 x 128 86 us, 128 x 128 99 us with two workgroups per
-  // CU and 44 us with one): the tiling with the least total.
+  // CU and 44 us with one): the tiling with the least total.  Of a row-layout operand the
+  // 256 x 128 tiles with 128-K steps take 0.8 (us at 5464 x 512, with 64-K steps, with
+  // these, 256 x 256, 128 x 128: 16384 rows 98, 77, 107, -; 65536 rows 401, 349, 300, -;
+  // 4096 rows 74, 62, 105, 53).
   const int64_t cus = device_cus(), t128 = cdiv(g.M, 128) * cdiv(g.N, 128), last = t128 % (2 * cus);
-  const double big = 1.25 * cdiv(cdiv(g.M, 256) * cdiv(g.N, 256), cus), mid = 1.0 * cdiv(cdiv(g.M, 256) * cdiv(g.N, 128), cus);
+  const double big = 1.25 * cdiv(cdiv(g.M, 256) * cdiv(g.N, 256), cus), mid = (g.a_tiled ? 1.0 : 0.8) * cdiv(cdiv(g.M, 256) * cdiv(g.N, 128), cus);
   const double small = 1.15 * (t128 / (2 * cus)) + (last == 0 ? 0.0 : last <= cus ? 0.51 : 1.15);
   if (small < mid && small < big) return launch<CfgSPs>(tag, g, 1, st);
-  if (mid < big) return launch<CfgSPn>(tag, g, 1, st);
+  if (mid < big) return g.a_tiled ? launch<CfgSPn>(tag, g, 1, st) : launch<CfgSPr>(tag, g, 1, st);
   return launch<CfgSP>(tag, g, 1, st);
 }
 // Epilogues that select and compress 2:4 groups (features along M).

@@ -17,7 +17,9 @@ def _ints(shape, seed, hi=3):
 
 
 @pytest.mark.parametrize("M,K,N", [(130, 200, 136), (4099, 328, 504), (9001, 200, 520), (16500, 264, 512),
-                                   (33001, 136, 256), (65537, 72, 264)])
+                                   (33001, 136, 256), (65537, 72, 264),
+                                   # 256 x 128 tiles with 128 K per step: a half step, one step and a half
+                                   (9001, 40, 520), (9001, 136, 520), (15001, 264, 512)])
 @pytest.mark.parametrize("layout", [elas.ELAS_B_KN, elas.ELAS_B_NK])
 def test_spmm_ragged(M, K, N, layout):
     h = _ints((M, K), M)
