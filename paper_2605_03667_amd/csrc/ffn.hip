@@ -333,7 +333,7 @@ bool resident_rank(int64_t r) { return r == 128 || r == 256 || r == 512; }
 // The d_ff-wide ones (up projection and dH) are faster than the tiled kernel at
 // every token count (microseconds, tiled against this: 60M at 512 tokens k2
 // 10.0 / 8.6, b3 11.6 / 9.5; 1B at 2048 29.5 / 21.3, 33.5 / 22.3; 1B at 65536
-// 424 / 307, 478 / 340), but where nothing else is laid out in the call, laying
+// 424 / 307, 478 / 334), but where nothing else is laid out in the call, laying
 // the weights out in fragment order is a launch of its own (6 to 10 us), which up
 // to 2048 tokens costs more than it gives.
 bool resident_wide(int64_t T, int64_t r, bool laid_out) { return resident_rank(r) && T > 0 && (laid_out || T > 2048); }
