@@ -206,9 +206,10 @@ int elas_lowrank_ffn_fwd(const uint16_t* x, const uint16_t* U_up, const uint16_t
  * library holds on every device it runs on until the process ends; the call
  * itself allocates nothing (no hipMalloc, no allocating library routine).
  * The first call on a device looks the array's address up there.
+ * Where elas_lowrank_ffn_fwd_workspace_bytes exceeds the array, kernels that
+ * need less are taken, as far as there are any.
  * Errors: as elas_lowrank_ffn_fwd, plus ELAS_ERR_WORKSPACE when the shape
- * needs more workspace than the array holds
- * (elas_lowrank_ffn_fwd_workspace_bytes > ELAS_NOALLOC_SCRATCH_BYTES; at the
+ * needs more workspace than the array holds even so (at the
  * largest model shape, d = 2048, d_ff = 5464, r = 512, it needs about 31 MB
  * at any token count), and ELAS_ERR_DEVICE if the address lookup fails.
  * Each call overwrites every part of the array it reads (nothing needs to

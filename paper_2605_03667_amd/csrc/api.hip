@@ -255,7 +255,11 @@ int elas_lowrank_ffn_fwd_noalloc(const uint16_t* x, const uint16_t* U_up, const 
   bool noop = false;
   ELAS_CHECK(prepare_fwd(x, U_up, V_up, U_down, V_down, T, d, d_ff, r, flags, y, P, s_vals, s_meta, Z, a, noop));
   if (noop) return ELAS_OK;
-  const size_t need = elas::fwd_workspace_bytes(T, d, d_ff, r, a.dense, a.ab);
+  size_t need = elas::fwd_workspace_bytes(T, d, d_ff, r, a.dense, a.ab);
+  if (need > kScratchBytes) {
+    a.lean = true;
+    need = elas::fwd_workspace_bytes(T, d, d_ff, r, a.dense, a.ab, true);
+  }
   if (need > kScratchBytes)
     return fail(ELAS_ERR_WORKSPACE, "this forward needs %zu bytes of workspace; the static scratch holds %zu",
                 need, kScratchBytes);

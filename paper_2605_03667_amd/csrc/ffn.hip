@@ -562,9 +562,20 @@ struct FwdWs {
   float* part;   // split-K partials of the long-K products at small token counts
   size_t bytes;
 };
+// The forward's kernels over K = r.  lean: without the token-resident ones, whose
+// factors in fragment order may not fit a workspace of a fixed size.
+Route fwd_up(int64_t T, int64_t F, int64_t r, bool dense, bool ab, bool lean) {
+  const Route w = route_wide(T, F, r, dense, !ab);
+  return lean && w == RESIDENT ? TILED : w;
+}
+Route fwd_down(int64_t T, int64_t d, int64_t r, bool lean) {
+  const Route w = route_down(T, d, r);
+  return lean && w == RESIDENT ? TILED : w;
+}
 // (ab: the caller passes the factors already K-contiguous; no copies)
-FwdWs fwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ab) {
+FwdWs fwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ab, bool lean) {
   const int64_t Fp = pad64(F);
+  const Route up = fwd_up(T, F, r, dense, ab, lean), down = fwd_down(T, d, r, lean);
   Carver c{p};
   FwdWs w{};
   if (!ab) {
@@ -572,8 +583,8 @@ FwdWs fwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bo
     w.U_downT = c.take<uint16_t>(r * Fp);
   }
   // (fragment order for the token-resident products, also from A and B)
-  if (!ab || route_wide(T, F, r, dense, !ab) == RESIDENT) w.V_upT = c.take<uint16_t>(Fp * r);
-  if (!ab || route_down(T, d, r) == RESIDENT) w.V_downT = c.take<uint16_t>(pad64(d) * r);
+  if (!ab || up == RESIDENT) w.V_upT = c.take<uint16_t>(Fp * r);
+  if (!ab || down == RESIDENT) w.V_downT = c.take<uint16_t>((down == RESIDENT ? pad64(d) : d) * r);
   size_t pb = small_split_bytes(T, r, d, 64);                 // k1
   pb = std::max(pb, small_split_bytes(T, r, Fp, 64));          // k3 (2:4 or dense)
   pb = std::max(pb, small_split_bytes(T, d, r, 64));           // k4
@@ -648,8 +659,8 @@ size_t spmm_workspace_bytes(int64_t K, int64_t N, int b_layout) {
   return b_layout == 0 ? align_up((size_t)K * N * sizeof(uint16_t)) : 0;
 }
 
-size_t fwd_workspace_bytes(int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ab) {
-  return fwd_ws(nullptr, T, d, F, r, dense, ab).bytes;
+size_t fwd_workspace_bytes(int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ab, bool lean) {
+  return fwd_ws(nullptr, T, d, F, r, dense, ab, lean).bytes;
 }
 
 size_t bwd_workspace_bytes(int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ste) {
@@ -676,14 +687,14 @@ hipError_t run_spmm24(const uint16_t* a_vals, const uint8_t* a_meta, int64_t M, 
 
 hipError_t run_fwd(const FfnArgs& a, hipStream_t st) {
   const int64_t T = a.T, d = a.d, F = a.F, r = a.r, Fp = pad64(F);
-  const FwdWs w = fwd_ws((char*)a.ws, T, d, F, r, a.dense, a.ab);
+  const FwdWs w = fwd_ws((char*)a.ws, T, d, F, r, a.dense, a.ab, a.lean);
   // Weight factors K-contiguous for the MFMA operands: laid out here, or
   // given so (ELAS_FACTORS_AB: unpadded d_ff, whose missing rows / columns
   // the loads read as zero, exactly like the zero padding of the copies).
   const uint16_t *U_upT = a.U_up, *V_upT = a.V_up, *U_downT = a.U_down, *V_downT = a.V_down;
   int64_t F_rows = F, ld_ud = F;   // rows of V_up^T, pitch (= K extent) of U_down^T
   const bool fused = !a.dense && a.fused == 1;
-  const Route up = fused ? TILED : route_wide(T, F, r, a.dense, !a.ab), down = fused ? TILED : route_down(T, d, r);
+  const Route up = fused ? TILED : fwd_up(T, F, r, a.dense, a.ab, a.lean), down = fused ? TILED : fwd_down(T, d, r, a.lean);
   // The token-resident products take V_up^T and V_down^T in fragment order.
   const int64_t kp_up = up == RESIDENT ? r / 64 : 0, kp_down = down == RESIDENT ? r / 64 : 0;
   Transposes tr;

@@ -56,6 +56,7 @@ struct FfnArgs {
   bool dense;   // activations dense [T x d_ff] (no 2:4 selection)
   bool ste;     // backward: straight-through estimator through the selection
   bool ab;      // forward: factors given as U_up^T, V_up^T, U_down^T, V_down^T
+  bool lean;    // forward: the smallest workspace (no weights in fragment order)
   int fused;    // sparse forward: 1 one fused launch, else (0 default, 2 requested) four kernels
 };
 
@@ -68,7 +69,7 @@ hipError_t run_fused_fwd(const uint16_t* x, const uint16_t* U_upT, const uint16_
 
 // ffn.hip
 size_t spmm_workspace_bytes(int64_t K, int64_t N, int b_layout);
-size_t fwd_workspace_bytes(int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ab);
+size_t fwd_workspace_bytes(int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ab, bool lean = false);
 size_t bwd_workspace_bytes(int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ste);
 hipError_t run_spmm24(const uint16_t* a_vals, const uint8_t* a_meta, int64_t M, int64_t K,
                       const uint16_t* b, int64_t N, bool b_is_nk, uint16_t* c, void* ws,

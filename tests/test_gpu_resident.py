@@ -32,3 +32,19 @@ def test_resident_factors_ab_identical(T, d, F, r):
     b = elas.elas_lowrank_ffn_fwd(t["x"], *[x.t().contiguous() for x in w], flags=elas.ELAS_FACTORS_AB)
     for k in a:
         assert torch.equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("mode", [0, elas.ELAS_MODE_DENSE])
+def test_noalloc_at_the_scratch_limit(mode):
+    """The weights in fragment order exceed the static scratch (64 MiB): the
+    forward takes the kernels that need less, whose sums over r run in the same
+    order.  (The long sums of Z are the same kernel's either way.)"""
+    T, d, F, r, flags = 2049, 64, 65536, 512, elas.ELAS_FACTORS_AB | mode
+    assert elas.elas_lowrank_ffn_fwd_workspace_bytes(T, d, F, r, flags) > elas.elas_noalloc_scratch_bytes()
+    t = {k: dev_bf16(v) for k, v in ffn_inputs(T, d, F, r, seed_base=9).items()}
+    w = [t[k].t().contiguous() for k in ("U_up", "V_up", "U_down", "V_down")]
+    a = elas.elas_lowrank_ffn_fwd(t["x"], *w, flags=flags)
+    out = {k: None if v is None else torch.full_like(v, 7) for k, v in a.items()}
+    b = elas.elas_lowrank_ffn_fwd_noalloc(t["x"], *w, flags=flags, out=out)
+    for k in a:
+        assert a[k] is None or torch.equal(a[k], b[k]), k
