@@ -378,58 +378,77 @@ hipError_t resident_bf16(const char* tag, const uint16_t* W, const uint16_t* X, 
 }
 
 // Wave-split products (small.h).
-template <int EPI, bool SP, int TT, int FI, int KS, int FW, int D>
-hipError_t launch_small_as(const char* tag, SmallArgs g, hipStream_t st) {
-  if (KS > 1 && g.chunk == 0) g.chunk = (int)cdiv(cdiv(g.K, 64), KS);
-  if (KS == 1) g.chunk = (int)cdiv(g.K, 64);
+template <int EPI, bool SP, int TT, int FI, int FW, int D, int MAXW>
+hipError_t launch_small_as(const char* tag, const SmallArgs& g, hipStream_t st) {
+  const int waves = g.ks * FW;
+  const size_t lds = (size_t)waves * FI * TT * 1024;
+  if (waves > MAXW || lds > 64 * 1024) return hipErrorInvalidValue;
   TimedLaunch tl(tag, st);
   const dim3 grid((unsigned)cdiv(g.M, FW * FI * 16), (unsigned)cdiv(g.T, TT * 16));
-  hipLaunchKernelGGL((small_kernel<EPI, SP, TT, FI, KS, FW, D>), grid, dim3(64 * KS * FW), 0, st, g);
+  hipLaunchKernelGGL((small_kernel<EPI, SP, TT, FI, FW, D, MAXW>), grid, dim3(64 * waves), lds, st, g);
   return hipGetLastError();
 }
-// Long contractions (over d or d_ff) to M features: K over 16 waves of a
-// workgroup with 16 features of 16 or 32 tokens, or over 8 with 32 features of
-// 64.  Taken as long as each CU has at most one workgroup; a second one per CU
-// doubles the time, and the tiled kernel wins (us, the tiled kernel and its reduce
-// against this one: k1 at 1B, 16 tokens 14.5 + 6.7 / 7.8, 256 12.0 + 6.2 / 9.8,
-// 1024 12.5 + 6.3 / 15.4; 350M at 2000 tokens 15.0 + 6.2 / 10.6; k3 at 1B, 16 tokens
-// 18.9 + 6.5 / 9.6, 256 13.9 + 6.2 / 12.8, 1024 15.7 + 6.3 / 20.5).
-int small_long_shape(int64_t T, int64_t M) {
-  const int64_t cus = device_cus();
-  if (T <= 0) return 0;
-  if (cdiv(M, 16) * cdiv(T, 32) <= cus) return T <= 16 ? 1 : 2;
-  return cdiv(M, 32) * cdiv(T, 64) <= cus ? 3 : 0;
+// Sums cut as the tiled product's split-K cuts them (one chunk where it is not split).
+SmallSplit tiled_chunks(int64_t T, int64_t M, int64_t K) {
+  return few_tiles(T, M, 256, 256) ? plan_small_split(T, M, K, 64) : SmallSplit{1, K};
+}
+// Long contractions (over d or d_ff) to M features, one wave per chunk of K.  Blocks
+// per wave: the fewest with which each CU has at most one workgroup, or two where
+// those are of few waves; with more the tiled kernel is ahead, and earlier where there
+// are many chunks.  Whole calls in us, tiled against 1 x 1, 2 x 1, 2 x 2, 4 x 1 and
+// 4 x 2 (token x feature) blocks:
+//   forward, k1:   60M, 1 chunk,  2048 tokens  34.9 | 33.2  32.6  31.5  33.5  33.4
+//                  350M, 2,       2000         47.7 | 50.6  47.1  44.3  45.6  43.4
+//                  1B, 4,         16           36.2 | 31.7  31.9  33.6  33.0  34.8
+//                                 256          52.7 | 49.2  47.3  49.2  50.9  53.0
+//                                 512          56.9 | 58.8  55.4  52.1  53.9  56.1
+//                                 1024         60.8 | 76.3  69.6  62.8  66.2  59.6
+//   forward, k3:   60M, 2,        4096         42.3 | 40.1  37.8  35.7  37.5  37.7
+//                  350M, 5,       2000         47.7 | 56.5  49.2  46.7  46.1  43.3
+//                  1B, 10,        512          56.9 | 67.0  55.9    -   52.4    -
+//                  1B, 8,         1024         60.8 | 84.8  71.8  67.8  66.2  61.3
+//   dense step, k3: 60M, 2,       2048         99.5 | 95.8  95.0  93.0  95.7  95.4
+//                  1B, 8,         1000        183.2 | 220   209   197   203   191
+//   the same and b5: 1B, 10,      512         156   |  -     -     -    150     -
+// 0: the tiled kernel; else the shape of launch_small_long.
+template <bool SP>
+int small_long_shape(int64_t T, int64_t M, const SmallSplit& p) {
+  if (T <= 0 || p.splits > 16) return 0;
+  const int64_t cus = device_cus(), m1 = cdiv(M, 16), m2 = cdiv(M, 32);
+  const int64_t most = p.splits <= (SP || M <= 128 ? 2 : 1) ? 2 * cus : cus;
+  if (m1 * cdiv(T, 16) <= most) return 1;
+  if (m1 * cdiv(T, 32) <= cus) return 2;
+  if (p.splits <= (SP ? 2 : 8) && m2 * cdiv(T, 32) <= most) return 3;
+  if (p.splits > (SP ? 2 : 8) && p.splits <= 12 && m1 * cdiv(T, 64) <= cus) return 4;
+  return p.splits <= 6 && m2 * cdiv(T, 64) <= cus ? 5 : 0;
 }
 template <bool SP>
-hipError_t launch_small_long(const char* tag, const SmallArgs& g, hipStream_t st) {
-  switch (small_long_shape(g.T, g.M)) {
-    case 1: return launch_small_as<EPI_BF16, SP, 1, 1, 16, 1, 3>(tag, g, st);
-    case 2: return launch_small_as<EPI_BF16, SP, 2, 1, 16, 1, 3>(tag, g, st);
-    default: return launch_small_as<EPI_BF16, SP, 4, 2, 8, 1, 2>(tag, g, st);
+hipError_t launch_small_long(const char* tag, SmallArgs g, const SmallSplit& p, hipStream_t st) {
+  g.ks = p.splits;
+  g.chunk = (int)cdiv(p.k_split, 64);
+  switch (small_long_shape<SP>(g.T, g.M, p)) {
+    case 1:   // (a lone wave row of few chunks: all of a short K in flight; 60M, 16 tokens, k3 18.4 -> 18.1)
+      if (p.splits <= 8 && cdiv(g.M, 16) * cdiv(g.T, 16) <= device_cus()) return launch_small_as<EPI_BF16, SP, 1, 1, 1, 8, 8>(tag, g, st);
+      return launch_small_as<EPI_BF16, SP, 1, 1, 1, 4, 16>(tag, g, st);
+    case 2: return launch_small_as<EPI_BF16, SP, 2, 1, 1, 3, 16>(tag, g, st);
+    case 3: return launch_small_as<EPI_BF16, SP, 2, 2, 1, 3, 8>(tag, g, st);
+    case 4: return launch_small_as<EPI_BF16, SP, 4, 1, 1, 3, 12>(tag, g, st);
+    case 5: return launch_small_as<EPI_BF16, SP, 4, 2, 1, 2, 8>(tag, g, st);
+    default: return hipErrorInvalidValue;
   }
 }
-// P = x U_up: a rounding of P decides what the selection ranks, so K is cut as
-// the tiled kernel's split-K cuts it (into 1, 2 or 4 chunks here) and P is the
-// same bits.
-template <int KS>
-hipError_t launch_small_k1_as(SmallArgs g, hipStream_t st) {
-  if (small_long_shape(g.T, g.M) == 1) return launch_small_as<EPI_BF16, false, 1, 1, KS, 1, 8>("k1_up_gemm", g, st);
-  if (small_long_shape(g.T, g.M) == 2) return launch_small_as<EPI_BF16, false, 2, 1, KS, 1, 4>("k1_up_gemm", g, st);
-  return launch_small_as<EPI_BF16, false, 4, 2, KS, 1, 2>("k1_up_gemm", g, st);
-}
-hipError_t launch_small_k1(SmallArgs g, const SmallSplit& p, hipStream_t st) {
-  g.chunk = (int)(p.k_split / 64);
-  if (p.splits == 1) return launch_small_k1_as<1>(g, st);
-  return p.splits == 2 ? launch_small_k1_as<2>(g, st) : launch_small_k1_as<4>(g, st);
-}
-// Short ones (over r): features over the waves, each with the whole of K (the
-// tiled kernel's order of sums), by the same measure (k2 at 1B, 64 tokens 19.0 /
-// 10.6; k4 at 1B, 256 tokens 11.4 / 9.9; k4 at 350M, 500 tokens 10.4 / 7.3).
+// Short ones (over r): features over the waves, each with the whole of K, by the same
+// measure (k2 at 1B, 64 tokens 19.0 / 10.6; k4 at 1B, 256 tokens 11.4 / 9.9; k4 at
+// 350M, 500 tokens 10.4 / 7.3).
 bool small_short(int64_t T, int64_t M) { return T > 0 && cdiv(M, 64) * cdiv(T, 32) <= device_cus(); }
+// (plain output, where the tiled kernel may cut K = r)
+bool small_short(int64_t T, int64_t M, int64_t K) { return small_short(T, M) && tiled_chunks(T, M, K).splits == 1; }
 template <int EPI>
-hipError_t launch_small_short(const char* tag, const SmallArgs& g, hipStream_t st) {
-  if (g.T <= 16) return launch_small_as<EPI, false, 1, 1, 1, 4, 8>(tag, g, st);
-  return launch_small_as<EPI, false, 2, 1, 1, 4, 4>(tag, g, st);
+hipError_t launch_small_short(const char* tag, SmallArgs g, hipStream_t st) {
+  g.ks = 1;
+  g.chunk = (int)cdiv(g.K, 64);
+  if (g.T <= 16) return launch_small_as<EPI, false, 1, 1, 4, 8, 4>(tag, g, st);
+  return launch_small_as<EPI, false, 2, 1, 4, 4, 4>(tag, g, st);
 }
 // C [T x M] = X W^T, W [M x K].
 SmallArgs small_dense(const uint16_t* W, int64_t ldw, int64_t M, int64_t K, const uint16_t* X, int64_t ldx, int64_t T, uint16_t* C) {
@@ -445,14 +464,17 @@ SmallArgs small_sp(const uint16_t* W, int64_t ldw, int64_t M, int64_t F, const u
   g.X = sv; g.Xm = sm; g.ldx = vals_ld(F); g.ldxm = meta_ld(F); g.T = T; g.C = C; g.ldc = M;
   return g;
 }
+// Y and dx.
+hipError_t launch_small_down(const char* tag, const SmallArgs& g, hipStream_t st) {
+  const SmallSplit p = tiled_chunks(g.T, g.M, g.K);
+  return p.splits == 1 ? launch_small_short<EPI_BF16>(tag, g, st) : launch_small_long<false>(tag, g, p, st);
+}
 // The kernel of each product of one call.
 enum Route { TILED, SMALL, RESIDENT };
-// Z, dZ and dP; P.
-Route route_long(int64_t T, int64_t M) { return small_long_shape(T, M) ? SMALL : TILED; }
-Route route_k1(int64_t T, int64_t d, int64_t r) {
-  const int n = plan_small_split(T, r, d, 64).splits;
-  return small_long_shape(T, r) && few_tiles(T, r, 256, r <= 128 ? 128 : 256) && (n <= 2 || n == 4) ? SMALL : TILED;
-}
+// P and dZ (K = d); Z and dP (K = d_ff, padded to 64 where the activation is compressed).
+template <bool SP>
+Route route_long(int64_t T, int64_t M, int64_t K) { return small_long_shape<SP>(T, M, tiled_chunks(T, M, K)) ? SMALL : TILED; }
+Route route_over_ff(int64_t T, int64_t F, int64_t r, bool sp) { return sp ? route_long<true>(T, r, pad64(F)) : route_long<false>(T, r, F); }
 // The up projection and masked dH (sparse mode) or their dense counterparts;
 // laid_out: the call lays out weights anyway.
 Route route_wide(int64_t T, int64_t F, int64_t r, bool dense, bool laid_out) {
@@ -461,7 +483,7 @@ Route route_wide(int64_t T, int64_t F, int64_t r, bool dense, bool laid_out) {
 }
 // Y and dx.
 Route route_down(int64_t T, int64_t d, int64_t r) {
-  if (small_short(T, d)) return SMALL;
+  if (small_short(T, d, r) || (tiled_chunks(T, d, r).splits > 1 && route_long<false>(T, d, r) == SMALL)) return SMALL;
   return resident_down(T, r) ? RESIDENT : TILED;
 }
 
@@ -593,6 +615,10 @@ FwdWs fwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bo
   return w;
 }
 
+// The tiled products of the backward take V_up and V_down laid out.
+bool bwd_lays_out(int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ste) {
+  return route_long<false>(T, r, d) == TILED || route_over_ff(T, F, r, !dense && !ste) == TILED;
+}
 struct BwdWs {
   uint16_t *dZ, *dH, *dP, *V_upT;
   uint16_t *U_downR, *U_upR;   // U_down and U_up in fragment order (token-resident products)
@@ -634,7 +660,7 @@ BwdWs bwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bo
   if (ste) w.V_upT = c.take<uint16_t>(Fp * r);
   w.V_upB = c.take<uint16_t>(pad256(r) * Fp);
   w.V_downB = c.take<uint16_t>(pad256(r) * pad64(d));
-  if (!ste && route_wide(T, F, r, dense, route_long(T, r) == TILED) == RESIDENT) w.U_downR = c.take<uint16_t>(Fp * r);
+  if (!ste && route_wide(T, F, r, dense, bwd_lays_out(T, d, F, r, dense, ste)) == RESIDENT) w.U_downR = c.take<uint16_t>(Fp * r);
   if (route_down(T, d, r) == RESIDENT) w.U_upR = c.take<uint16_t>(pad64(d) * r);
   // partials: the weight gradients', and split-K of the long-K bf16 products at
   // small token counts (b1, b5, b8)
@@ -723,8 +749,8 @@ hipError_t run_fwd(const FfnArgs& a, hipStream_t st) {
     return run_fused_fwd(a.x, U_upT, V_upT, U_downT, V_downT, T, d, F, r, F_rows, ld_ud, a.y, a.P, a.s_vals,
                          a.s_meta, a.Z, st);
   // P = x U_up
-  if (route_k1(T, d, r) == SMALL)
-    ELAS_TRY(launch_small_k1(small_dense(U_upT, d, r, d, a.x, d, T, a.P), plan_small_split(T, r, d, 64), st));
+  if (route_long<false>(T, r, d) == SMALL)
+    ELAS_TRY(launch_small_long<false>("k1_up_gemm", small_dense(U_upT, d, r, d, a.x, d, T, a.P), tiled_chunks(T, r, d), st));
   else
     ELAS_TRY(gemm_nt_bf16("k1_up_gemm", a.x, d, U_upT, d, a.P, r, T, r, d, st, w.part));
   ResArgs q{};   // the up projection
@@ -748,8 +774,8 @@ hipError_t run_fwd(const FfnArgs& a, hipStream_t st) {
       ELAS_TRY(launch_staged<EPI_SPARSIFY>(tag, g, st));
     }
     // Z = S U_down on the 2:4 operand
-    if (route_long(T, r) == SMALL) {
-      ELAS_TRY(launch_small_long<true>("k3_spmm_down", small_sp(U_downT, ld_ud, r, F, a.s_vals, a.s_meta, T, a.Z), st));
+    if (route_long<true>(T, r, Fp) == SMALL) {
+      ELAS_TRY(launch_small_long<true>("k3_spmm_down", small_sp(U_downT, ld_ud, r, F, a.s_vals, a.s_meta, T, a.Z), tiled_chunks(T, r, Fp), st));
     } else {
       GemmArgs z{};
       z.A = a.s_vals; z.lda = vals_ld(F); z.Am = a.s_meta; z.ldam = meta_ld(F); z.a_tiled = 1; z.tok = T;
@@ -767,13 +793,13 @@ hipError_t run_fwd(const FfnArgs& a, hipStream_t st) {
     } else {
       ELAS_TRY(gemm_nt<EPI_ACT_DENSE>(tag, a.P, r, V_upT, r, a.s_vals, F, T, F, r, st));
     }
-    if (route_long(T, r) == SMALL)
-      ELAS_TRY(launch_small_long<false>("k3_down_gemm_dense", small_dense(U_downT, ld_ud, r, F, a.s_vals, F, T, a.Z), st));
+    if (route_long<false>(T, r, F) == SMALL)
+      ELAS_TRY(launch_small_long<false>("k3_down_gemm_dense", small_dense(U_downT, ld_ud, r, F, a.s_vals, F, T, a.Z), tiled_chunks(T, r, F), st));
     else
       ELAS_TRY(gemm_nt_bf16("k3_down_gemm_dense", a.s_vals, F, U_downT, ld_ud, a.Z, r, T, r, F, st, w.part));
   }
   // Y = Z V_down
-  if (down == SMALL) return launch_small_short<EPI_BF16>("k4_down_gemm", small_dense(V_downT, r, d, r, a.Z, r, T, a.y), st);
+  if (down == SMALL) return launch_small_down("k4_down_gemm", small_dense(V_downT, r, d, r, a.Z, r, T, a.y), st);
   if (down == RESIDENT) return resident_bf16("k4_down_gemm", V_downT, a.Z, T, d, r, a.y, st);
   ELAS_TRY(gemm_nt_bf16("k4_down_gemm", a.Z, r, V_downT, r, a.y, d, T, d, r, st, w.part));
   return hipSuccess;
@@ -809,28 +835,27 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
   // cache lines.  Both are copied blocked (one contiguous 32 KB block per
   // tile K step: measured 7 % faster for dP at 1B), and V_up^T for the
   // straight-through backward, in one launch.
-  const Route lng = route_long(T, r), down = route_down(T, d, r);
-  const Route wide = a.ste ? TILED : route_wide(T, F, r, a.dense, lng == TILED);
+  const bool sp = !a.dense && !a.ste;   // dH compressed
+  const Route rz = route_long<false>(T, r, d), rp = route_over_ff(T, F, r, sp), down = route_down(T, d, r);
+  const Route wide = a.ste ? TILED : route_wide(T, F, r, a.dense, bwd_lays_out(T, d, F, r, a.dense, a.ste));
   const int64_t nsk_vu = Fp / 64, nsk_vd = pad64(d) / 64;
   {
     Transposes tr;
-    if (lng == TILED) {
-      tr.add(a.V_up, r, F, F, w.V_upB, pad256(r), Fp, 0, 0, nsk_vu);
-      tr.add(a.V_down, r, d, d, w.V_downB, pad256(r), pad64(d), 0, 0, nsk_vd);
-    }
+    if (rp == TILED) tr.add(a.V_up, r, F, F, w.V_upB, pad256(r), Fp, 0, 0, nsk_vu);
+    if (rz == TILED) tr.add(a.V_down, r, d, d, w.V_downB, pad256(r), pad64(d), 0, 0, nsk_vd);
     if (a.ste) tr.add(a.V_up, r, F, F, w.V_upT, Fp, r, r);      // [Fp x r], zero rows >= F
     if (wide == RESIDENT) tr.add(a.U_down, F, r, r, w.U_downR, Fp, r, r, 0, 0, r / 64);
     if (down == RESIDENT) tr.add(a.U_up, d, r, r, w.U_upR, pad64(d), r, r, 0, 0, r / 64);
     ELAS_TRY(tr.launch(st));
   }
   // dZ = dY V_down^T
-  if (lng == SMALL)
-    ELAS_TRY(launch_small_long<false>("b1_dZ", small_dense(a.V_down, d, r, d, a.dy, d, T, w.dZ), st));
+  if (rz == SMALL)
+    ELAS_TRY(launch_small_long<false>("b1_dZ", small_dense(a.V_down, d, r, d, a.dy, d, T, w.dZ), tiled_chunks(T, r, d), st));
   else
     ELAS_TRY(gemm_nt_bf16("b1_dZ", a.dy, d, w.V_downB, d, w.dZ, r, T, r, d, st, w.part, nsk_vd));
   ResArgs q{};   // dS = dZ U_down^T
   q.W = w.U_downR; q.X = w.dZ; q.ldx = r; q.T = T; q.nfb = (int)(Fp / 64);
-  if (!a.dense && !a.ste) {
+  if (sp) {
     // dH = (dZ U_down^T) * mask * 2 relu(H), computed as dS^T = U_down dZ^T
     const char* tag = "b3_dH_masked";
     q.sv = a.s_vals; q.sm = a.s_meta; q.ldv = ldv; q.ldm = ldm; q.dv = w.dH;
@@ -849,8 +874,8 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
       ELAS_TRY(launch_staged<EPI_DH>(tag, g, st));
     }
     // dP = dH V_up^T on the 2:4 operand (tiled kernel: V_up blocked)
-    if (lng == SMALL) {
-      ELAS_TRY(launch_small_long<true>("b5_spmm_dP", small_sp(a.V_up, F, r, F, w.dH, a.s_meta, T, w.dP), st));
+    if (rp == SMALL) {
+      ELAS_TRY(launch_small_long<true>("b5_spmm_dP", small_sp(a.V_up, F, r, F, w.dH, a.s_meta, T, w.dP), tiled_chunks(T, r, Fp), st));
     } else {
       GemmArgs p{};
       p.A = w.dH; p.lda = ldv; p.Am = a.s_meta; p.ldam = ldm; p.a_tiled = 1; p.tok = T;
@@ -881,8 +906,8 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
       ELAS_TRY(launch_act<EPI_DH_DENSE>("b3_dH_dense", g, st));
     }
     // dP = dH V_up^T (dense)
-    if (lng == SMALL)
-      ELAS_TRY(launch_small_long<false>("b5_dP_dense", small_dense(a.V_up, F, r, F, w.dH, Fp, T, w.dP), st));
+    if (rp == SMALL)
+      ELAS_TRY(launch_small_long<false>("b5_dP_dense", small_dense(a.V_up, F, r, F, w.dH, Fp, T, w.dP), tiled_chunks(T, r, F), st));
     else
       ELAS_TRY(gemm_nt_bf16("b5_dP_dense", w.dH, Fp, w.V_upB, F, w.dP, r, T, r, F, st, w.part, nsk_vu));
   }
@@ -890,7 +915,7 @@ hipError_t run_bwd(const FfnArgs& a, hipStream_t st) {
   ELAS_TRY(wgrad_plan(a, w, a.dense, a.ste).launch(a.dense ? "b2467_weight_grads_dense" : a.ste ? "b2467_weight_grads_ste"
                                                                                              : "b2467_weight_grads", st));
   // dx = dP U_up^T   (U_up [d x r] is already K-contiguous)
-  if (down == SMALL) return launch_small_short<EPI_BF16>("b8_dx", small_dense(a.U_up, r, d, r, w.dP, r, T, a.dx), st);
+  if (down == SMALL) return launch_small_down("b8_dx", small_dense(a.U_up, r, d, r, w.dP, r, T, a.dx), st);
   if (down == RESIDENT) return resident_bf16("b8_dx", w.U_upR, w.dP, T, d, r, a.dx, st);
   ELAS_TRY(gemm_nt_bf16("b8_dx", w.dP, r, a.U_up, r, a.dx, d, T, d, r, st, w.part));
   return hipSuccess;

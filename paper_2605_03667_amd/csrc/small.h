@@ -2,23 +2,28 @@
 // kernel would leave most CUs idle or need split-K partials in memory and a
 // second launch to add them.
 //
-// A workgroup of KS x FW waves owns FW x FI x 16 output features of TT x 16
-// tokens.  Its KS wave rows each take a contiguous chunk of K, load both
+// A workgroup of ks x FW waves owns FW x FI x 16 output features of TT x 16
+// tokens.  Its ks wave rows each take a contiguous chunk of K, load both
 // operands from memory straight into MFMA fragments (D 64-wide steps in flight,
 // no LDS on the way) and leave their sums in LDS; after one barrier the waves
-// add the KS partial sums in order (deterministic) and run the epilogue.  Bound by
+// add the ks partial sums in order (deterministic) and run the epilogue.  Bound by
 // latency: what counts is the number of launches and the loads in flight.  The
 // weights are read as a K-contiguous [features x K] matrix, so that nothing is
 // laid out first.
 //
-// Fragment layout (v_mfma_f32_16x16x32_bf16, two per step): lane l takes row
-// (feature or token) l % 16 and, for MFMA h, the 8 K entries from 32 h + 8 (l / 16)
-// of the step.  A 2:4 operand is read 16 bytes of kept values at a time, so
-// there (in both operands) they are those from 16 (l / 16) + 8 h.  With dense
-// operands and the chunks of a split-K tiled product the sums therefore run in
-// the tiled kernel's order and the results are the same bits.  The accumulators
-// of lane l are features 4 (l / 16) .. + 3 of token l % 16: one whole group of 4
-// (Algorithm 1).
+// The chunks are those of the tiled kernels' split-K, and within a chunk the sums
+// run in the tiled kernels' order, so that the results are the same bits and a
+// call's outputs do not depend on which of the two computes them.
+//
+// Fragment layout: of a 64-wide step, lane l takes of a dense operand row (feature
+// or token) l % 16 at K 8 (l / 16) .. + 7 and 32 + 8 (l / 16) .. + 7.  Dense
+// products take two v_mfma_f32_16x16x32_bf16, whose accumulators in lane l are
+// features 4 (l / 16) .. + 3 of token l % 16: one whole group of 4 (Algorithm 1).
+// A 2:4 operand is consumed by one v_smfmac_f32_16x16x64_bf16 (layout pinned by a
+// probe: lane l holds the kept values of row l % 16 at dense K 16 (l / 16) .. + 15,
+// its partner as above; the sums are those of two v_smfmac_f32_32x32x32_bf16 as the
+// tiled kernel feeds them).  It must be the instruction's first operand, so there
+// the accumulators are tokens 4 (l / 16) .. + 3 of feature l % 16.
 #pragma once
 
 #include "gemm.h"
@@ -30,7 +35,7 @@ struct SmallArgs {
   int64_t ldw;
   int m_valid, kw_valid;   // (dense tokens: kw_valid = K)
   int M, K;            // output features (SPARSIFY / DH: padded to 64) and contraction length
-  int chunk;           // 64-wide K steps per wave row
+  int chunk, ks;       // 64-wide K steps per wave row, wave rows
   const uint16_t* X;   // dense tokens [T x K], pitch ldx; or kept values of a 2:4 operand, tiled, pitch ldx
   const uint8_t* Xm;   // its metadata, tiled, pitch ldxm
   int64_t ldx, ldxm, T;
@@ -42,16 +47,16 @@ struct SmallArgs {
   uint16_t* dv;        // DH: kept values of dH, written
 };
 
-template <int EPI, bool SP, int TT, int FI, int KS, int FW, int D>
-__global__ __launch_bounds__(64 * KS * FW) void small_kernel(const SmallArgs g) {
-  constexpr int NW = KS * FW, FR = FI * TT;   // 16 x 16 blocks per wave
-  __shared__ __attribute__((aligned(16))) f32x4 part[KS][FW * FR][64];
+// MAXW: the most waves it is launched with (ks x FW; 8 leave each wave 256 registers, 16 leave 128).
+template <int EPI, bool SP, int TT, int FI, int FW, int D, int MAXW>
+__global__ __launch_bounds__(64 * MAXW) void small_kernel(const SmallArgs g) {
+  constexpr int FR = FI * TT;   // 16 x 16 blocks per wave
+  extern __shared__ __attribute__((aligned(16))) f32x4 part[];   // [ks][FW * FR][64]
   const int lane = threadIdx.x & 63, l16 = lane & 15, lg = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int ks = wave / FW, fw = wave % FW;
+  const int ks = wave / FW, fw = wave % FW, nw = g.ks * FW;
   const int64_t t0 = (int64_t)blockIdx.y * (TT * 16);
-  const int k_lane = lg * (SP ? 16 : 8);       // the lane's K offset in a step, and from MFMA 0 to MFMA 1
-  constexpr int k_half = SP ? 8 : 32;
+  const int k_lane = lg * 8;                   // the lane's K offset in a step (and 32 more)
   const int f0 = (int)blockIdx.x * (FW * FI * 16) + fw * FI * 16;
 
   // (rows past the end re-read the last one; their results are not stored, or
@@ -62,19 +67,17 @@ __global__ __launch_bounds__(64 * KS * FW) void small_kernel(const SmallArgs g) 
     const int f = f0 + i * 16 + l16;
     wrow[i] = g.W + (int64_t)(f < g.m_valid ? f : g.m_valid - 1) * g.ldw + k_lane;
   }
-  const uint16_t* xrow[TT];
-  const uint8_t* mrow[SP ? TT : 1];
-  int xstep[SP ? TT : 1], mstep[SP ? TT : 1];
+  // (2:4: a workgroup's tokens lie in one block of 256 rows, R of which exist)
+  const int64_t tb = t0 & ~(int64_t)255;
+  const int R = (int)(g.T - tb < 256 ? g.T - tb : 256);
+  const uint16_t* xrow[SP ? 1 : TT];
+  uint32_t xoff[SP ? TT : 1], moff[SP ? TT : 1];
 #pragma unroll
   for (int j = 0; j < TT; ++j) {
     const int64_t t = t0 + j * 16 + l16 < g.T ? t0 + j * 16 + l16 : g.T - 1;
     if constexpr (SP) {
-      const int64_t tb = t & ~(int64_t)255;
-      const int R = (int)(g.T - tb < 256 ? g.T - tb : 256);
-      xrow[j] = g.X + tb * g.ldx + (t - tb) * 32 + lg * 8;
-      mrow[j] = g.Xm + tb * g.ldxm + (t - tb) * 8 + lg * 2;
-      xstep[j] = R * 32;
-      mstep[j] = R * 8;
+      xoff[j] = (uint32_t)((t - tb) * 32 + lg * 8);
+      moff[j] = (uint32_t)((t - tb) * 8 + lg * 2);
     } else {
       xrow[j] = g.X + t * g.ldx + k_lane;
     }
@@ -93,28 +96,30 @@ __global__ __launch_bounds__(64 * KS * FW) void small_kernel(const SmallArgs g) 
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
 #pragma unroll
-        for (int i = 0; i < FI; ++i) a[d][i][h] = *(const uint4*)(wrow[i] + s * 64 + k_half * h);
+        for (int i = 0; i < FI; ++i) a[d][i][h] = *(const uint4*)(wrow[i] + s * 64 + 32 * h);
         if constexpr (!SP) {
 #pragma unroll
-          for (int j = 0; j < TT; ++j) b[d][j][h] = *(const uint4*)(xrow[j] + s * 64 + k_half * h);
+          for (int j = 0; j < TT; ++j) b[d][j][h] = *(const uint4*)(xrow[j] + s * 64 + 32 * h);
         }
       }
     } else {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
 #pragma unroll
-        for (int i = 0; i < FI; ++i) a[d][i][h] = load16(wrow[i] + s * 64 + k_half * h, k + k_half * h < g.kw_valid);
+        for (int i = 0; i < FI; ++i) a[d][i][h] = load16(wrow[i] + s * 64 + 32 * h, k + 32 * h < g.kw_valid);
         if constexpr (!SP) {
 #pragma unroll
-          for (int j = 0; j < TT; ++j) b[d][j][h] = load16(xrow[j] + s * 64 + k_half * h, k + k_half * h < g.kw_valid);
+          for (int j = 0; j < TT; ++j) b[d][j][h] = load16(xrow[j] + s * 64 + 32 * h, k + 32 * h < g.kw_valid);
         }
       }
     }
     if constexpr (SP) {
+      const uint16_t* xs = (const uint16_t*)uniform_ptr(g.X + tb * g.ldx + (int64_t)s * R * 32);
+      const uint8_t* ms = (const uint8_t*)uniform_ptr(g.Xm + tb * g.ldxm + (int64_t)s * R * 8);
 #pragma unroll
       for (int j = 0; j < TT; ++j) {
-        b[d][j][0] = *(const uint4*)(xrow[j] + (int64_t)s * xstep[j]);
-        m[d][j] = *(const uint16_t*)(mrow[j] + (int64_t)s * mstep[j]);
+        b[d][j][0] = *(const uint4*)(xs + xoff[j]);
+        m[d][j] = *(const uint16_t*)(ms + moff[j]);
       }
     }
   };
@@ -131,21 +136,25 @@ __global__ __launch_bounds__(64 * KS * FW) void small_kernel(const SmallArgs g) 
 #pragma unroll
     for (int d = 0; d < D; ++d) {
       if (s + d < s_end) {
+        if constexpr (SP) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+          for (int i = 0; i < FI; ++i) {
+            const bf16x16 w = __builtin_shufflevector(__builtin_bit_cast(bf16x8, a[d][i][0]), __builtin_bit_cast(bf16x8, a[d][i][1]),
+                                                      0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
 #pragma unroll
-          for (int j = 0; j < TT; ++j) {
-            uint4 x;
-            if constexpr (SP)
-              x = h == 0 ? expand2(make_uint2(b[d][j][0].x, b[d][j][0].y), m[d][j] & 0xFFu)
-                         : expand2(make_uint2(b[d][j][0].z, b[d][j][0].w), m[d][j] >> 8);
-            else
-              x = b[d][j][h];
-#pragma unroll
-            for (int i = 0; i < FI; ++i)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[d][i][h]),
-                                                                  __builtin_bit_cast(bf16x8, x), acc[i][j], 0, 0, 0);
+            for (int j = 0; j < TT; ++j)
+              acc[i][j] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(bf16x8, b[d][j][0]), w, acc[i][j], (int)m[d][j], 0, 0);
           }
+        } else {
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int j = 0; j < TT; ++j)
+#pragma unroll
+              for (int i = 0; i < FI; ++i)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[d][i][h]),
+                                                                    __builtin_bit_cast(bf16x8, b[d][j][h]), acc[i][j], 0, 0, 0);
+        }
         if (s + D + d < s_end) load(s + D + d, d);
       }
     }
@@ -153,24 +162,31 @@ __global__ __launch_bounds__(64 * KS * FW) void small_kernel(const SmallArgs g) 
 #pragma unroll
   for (int i = 0; i < FI; ++i)
 #pragma unroll
-    for (int j = 0; j < TT; ++j) part[ks][fw * FR + i * TT + j][lane] = acc[i][j];
+    for (int j = 0; j < TT; ++j) part[((ks * FW + fw) * FR + i * TT + j) * 64 + lane] = acc[i][j];
   __syncthreads();
-  for (int q = wave; q < FW * FR; q += NW) {
-    f32x4 c = part[0][q][lane];
-#pragma unroll
-    for (int k = 1; k < KS; ++k) c += part[k][q][lane];
+  for (int q = wave; q < FW * FR; q += nw) {
+    f32x4 c = part[q * 64 + lane];
+    for (int k = 1; k < g.ks; ++k) c += part[(k * FW * FR + q) * 64 + lane];
     const int fb = (int)blockIdx.x * (FW * FI * 16) + (q / FR) * FI * 16 + (q % FR / TT) * 16;   // the block's first feature
     const int64_t t = t0 + (q % TT) * 16 + l16;
     if (fb >= g.M) continue;   // (uniform over the wave)
     const bool ok = t < g.T;
+    if constexpr (SP) {
+      // tokens 4 lg .. + 3 of feature fb + l16
+      static_assert(EPI == EPI_BF16, "2:4 products: plain output");
+      const int f = fb + l16;
+      const int64_t ts = t0 + (q % TT) * 16 + 4 * lg;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (f < g.M && ts + e < g.T) g.C[(ts + e) * g.ldc + f] = (uint16_t)bf16x2_rne(c[e], 0.f);
+      continue;
+    }
     if (EPI != EPI_BF16 && fb + 4 * lg >= g.m_valid) c = f32x4{0.f, 0.f, 0.f, 0.f};
     if constexpr (EPI == EPI_BF16) {
       const int f = fb + 4 * lg;
       if (ok && f < g.M) *(uint2*)(g.C + t * g.ldc + f) = make_uint2(bf16x2_rne(c[0], c[1]), bf16x2_rne(c[2], c[3]));
     } else {
       // group (fb % 64) / 4 + lg of the token's 64-feature entry block
-      const int64_t tb = t & ~(int64_t)255;
-      const int64_t R = g.T - tb < 256 ? g.T - tb : 256;
       const int64_t iv = tb * g.ldv + (fb >> 6) * R * 32 + (t - tb) * 32 + (fb & 63) / 2 + 2 * lg;
       const int64_t im = tb * g.ldm + (fb >> 6) * R * 8 + (t - tb) * 8 + (fb & 63) / 8;
       if constexpr (EPI == EPI_SPARSIFY) {
