@@ -334,13 +334,32 @@ bool resident_rank(int64_t r) { return r == 128 || r == 256 || r == 512; }
 // every token count (microseconds, tiled against this: 60M at 512 tokens k2
 // 10.0 / 8.6, b3 11.6 / 9.5; 1B at 2048 29.5 / 21.3, 33.5 / 22.3; 1B at 65536
 // 424 / 307, 478 / 334), but where nothing else is laid out in the call, laying
-// the weights out in fragment order is a launch of its own (6 to 10 us), which up
-// to 2048 tokens costs more than it gives.
-bool resident_wide(int64_t T, int64_t r, bool laid_out) { return resident_rank(r) && T > 0 && (laid_out || T > 2048); }
+// the weights out in fragment order is a launch of its own.  It pays for itself from
+// 2049 tokens, unless the tiled kernel has them all in one round of tiles (at r = 256
+// in a full one); at dense activations from about 12 G multiplications.  Whole
+// forwards with the factors as a linear layer stores them, us, both products tiled
+// against this with its layout (and Y, below, as it is there): 60M at 4096 tokens
+// 30.8 / 32.5, at 8192 43.9 / 45.7, at 12000 55.5 / 53.5; 130M at 4096 45.0 / 50.7, at
+// 6000 57.3 / 56.1, at 8192 58.9 / 60.8, at 16384 82.2 / 78.1; 350M at 3000 56.8 / 54.3;
+// 1B at 2049 84.2 / 77.4; dense 60M at 8192 43.1 / 46.5, 130M at 16384 81.8 / 84.9 and at
+// 32768 140 / 135, 350M at 16384 103 / 107 and at 32768 200 / 191, 1B at 4096
+// 116 / 122 and at 6000 162 / 158.
+bool own_layout_pays(int64_t T, int64_t F, int64_t r, bool dense) {
+  if (T <= 2048) return false;
+  const int64_t Fp = pad64(F), cus = device_cus();
+  if (dense) return (double)T * Fp * r > 1.2e10;
+  const int64_t tiles = cdiv(Fp, 256) * cdiv(T, few_tiles(Fp, T, 256, 256) ? 128 : 256);   // of launch_staged
+  const bool one_round = r <= 128 ? tiles <= cus : r <= 256 && tiles <= cus && 8 * tiles > 7 * cus;
+  return !one_round;
+}
+bool resident_wide(int64_t T, int64_t F, int64_t r, bool dense, bool laid_out) {
+  return resident_rank(r) && T > 0 && (laid_out || own_layout_pays(T, F, r, dense));
+}
 // The d-wide ones (Y and dx), whose few features leave a split-K or 128-wide
-// tiling ahead up to 2048 tokens (1B, k4: 12.6 / 18.4 at 2048, 21.5 / 18.9 at
-// 3000, 149 / 137 at 65536; 60M 7.5 / 8.1, 7.8 / 8.4 and 24.3 / 21.0).
-bool resident_down(int64_t T, int64_t r) { return resident_rank(r) && T > 2048; }
+// tiling ahead up to 4096 tokens (whole forwards, tiled / this: 60M at 4096 31.6 / 32.5,
+// 130M 47.9 / 50.7, 350M 57.6 / 58.6, 1B 105.4 / 108.5; at 32768 70.8 / 70.8,
+// 122 / 117, 161 / 159, 460 / 454; training steps of 4096 1.5 to 0 % less tiled).
+bool resident_down(int64_t T, int64_t r) { return resident_rank(r) && T > 4096; }
 // Workgroups per block of 128 tokens: the split of the nfb 64-feature blocks
 // with the fewest rounds of wave tiles (copying the tokens costs about 0.4 of
 // one).
@@ -479,7 +498,7 @@ Route route_over_ff(int64_t T, int64_t F, int64_t r, bool sp) { return sp ? rout
 // laid_out: the call lays out weights anyway.
 Route route_wide(int64_t T, int64_t F, int64_t r, bool dense, bool laid_out) {
   if (!dense && small_short(T, pad64(F))) return SMALL;
-  return resident_wide(T, r, laid_out) ? RESIDENT : TILED;
+  return resident_wide(T, F, r, dense, laid_out) ? RESIDENT : TILED;
 }
 // Y and dx.
 Route route_down(int64_t T, int64_t d, int64_t r) {
@@ -590,14 +609,15 @@ Route fwd_up(int64_t T, int64_t F, int64_t r, bool dense, bool ab, bool lean) {
   const Route w = route_wide(T, F, r, dense, !ab);
   return lean && w == RESIDENT ? TILED : w;
 }
-Route fwd_down(int64_t T, int64_t d, int64_t r, bool lean) {
+// (a layout launch for Y alone does not pay)
+Route fwd_down(int64_t T, int64_t d, int64_t r, bool lean, bool ab, Route up) {
   const Route w = route_down(T, d, r);
-  return lean && w == RESIDENT ? TILED : w;
+  return (lean || (ab && up != RESIDENT)) && w == RESIDENT ? TILED : w;
 }
 // (ab: the caller passes the factors already K-contiguous; no copies)
 FwdWs fwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ab, bool lean) {
   const int64_t Fp = pad64(F);
-  const Route up = fwd_up(T, F, r, dense, ab, lean), down = fwd_down(T, d, r, lean);
+  const Route up = fwd_up(T, F, r, dense, ab, lean), down = fwd_down(T, d, r, lean, ab, up);
   Carver c{p};
   FwdWs w{};
   if (!ab) {
@@ -720,7 +740,7 @@ hipError_t run_fwd(const FfnArgs& a, hipStream_t st) {
   const uint16_t *U_upT = a.U_up, *V_upT = a.V_up, *U_downT = a.U_down, *V_downT = a.V_down;
   int64_t F_rows = F, ld_ud = F;   // rows of V_up^T, pitch (= K extent) of U_down^T
   const bool fused = !a.dense && a.fused == 1;
-  const Route up = fused ? TILED : fwd_up(T, F, r, a.dense, a.ab, a.lean), down = fused ? TILED : fwd_down(T, d, r, a.lean);
+  const Route up = fused ? TILED : fwd_up(T, F, r, a.dense, a.ab, a.lean), down = fused ? TILED : fwd_down(T, d, r, a.lean, a.ab, up);
   // The token-resident products take V_up^T and V_down^T in fragment order.
   const int64_t kp_up = up == RESIDENT ? r / 64 : 0, kp_down = down == RESIDENT ? r / 64 : 0;
   Transposes tr;
