@@ -99,8 +99,11 @@ extern "C" {
 #define ELAS_FACTORS_AB      8u /* the factors are given as the A and B of Eq. 1 (W = A B, the
                                    orientation a linear layer stores): U_up^T [r,d],
                                    V_up^T [d_ff,r], U_down^T [r,d_ff], V_down^T [d,r].  This is
-                                   the kernels' operand layout, so nothing is re-laid out (for
-                                   inference with pre-arranged weights); results are identical */
+                                   the kernels' operand layout (for inference with pre-arranged
+                                   weights); results are identical.  From 2049 tokens, at r = 128,
+                                   256 or 512, the call may copy V_up and V_down into another
+                                   order in its workspace, where that makes it faster; given a
+                                   workspace too small for that it copies nothing               */
 
 /* elas_lowrank_ffn_fwd only, sparse mode: launch shape.  Without either flag the forward is
    the four-kernel sequence (on MI355X faster than the fused launch at every supported shape
@@ -184,7 +187,9 @@ int elas_spmm_24(const uint16_t* a_vals, const uint8_t* a_meta, int64_t M, int64
  * ranks max(0, bf16(H))^2 exactly, ties to the lower index.
  * flags: ELAS_MODE_SPARSE24 (0) or ELAS_MODE_DENSE, optionally | ELAS_FACTORS_AB
  *   (the four factor pointers then hold the transposed matrices listed there).
- * workspace >= elas_lowrank_ffn_fwd_workspace_bytes(T, d, d_ff, r, flags).  The
+ * workspace >= elas_lowrank_ffn_fwd_workspace_bytes(T, d, d_ff, r, flags) (with
+ * ELAS_FACTORS_AB less, or none, is accepted where only copies of factors would
+ * need it: the same results from slower kernels; else ELAS_ERR_WORKSPACE).  The
  * size depends on T and is not monotonic in it (small token counts add fp32
  * split-K partials), so query it for every T a buffer is reused for.
  * Requires T >= 0, d, d_ff, r > 0, multiples of 8 and at most 65536.  T == 0 is

@@ -120,6 +120,17 @@ int prepare_fwd(const uint16_t* x, const uint16_t* U_up, const uint16_t* V_up, c
   return ELAS_OK;
 }
 
+// Workspace bytes of the forward: of the kernels that have is enough for (a.lean), or
+// else of those that need the least.
+size_t fwd_need(elas::FfnArgs& a, size_t have) {
+  size_t need = elas::fwd_workspace_bytes(a.T, a.d, a.F, a.r, a.dense, a.ab);
+  if (need > have) {
+    a.lean = true;
+    need = elas::fwd_workspace_bytes(a.T, a.d, a.F, a.r, a.dense, a.ab, true);
+  }
+  return need;
+}
+
 // Workspace of elas_lowrank_ffn_fwd_noalloc: one static array per device,
 // held until the process ends.  Its device address is looked up once per
 // device (with that device current) and kept; the array's name is only a
@@ -235,7 +246,7 @@ int elas_lowrank_ffn_fwd(const uint16_t* x, const uint16_t* U_up, const uint16_t
   bool noop = false;
   ELAS_CHECK(prepare_fwd(x, U_up, V_up, U_down, V_down, T, d, d_ff, r, flags, y, P, s_vals, s_meta, Z, a, noop));
   if (noop) return ELAS_OK;
-  const size_t need = elas::fwd_workspace_bytes(T, d, d_ff, r, a.dense, a.ab);
+  const size_t need = fwd_need(a, workspace_bytes);
   if (workspace_bytes < need)
     return fail(ELAS_ERR_WORKSPACE, "workspace %zu bytes, %zu needed", workspace_bytes, need);
   if (need) ELAS_CHECK(check_ptr(workspace, "workspace"));
@@ -255,11 +266,7 @@ int elas_lowrank_ffn_fwd_noalloc(const uint16_t* x, const uint16_t* U_up, const 
   bool noop = false;
   ELAS_CHECK(prepare_fwd(x, U_up, V_up, U_down, V_down, T, d, d_ff, r, flags, y, P, s_vals, s_meta, Z, a, noop));
   if (noop) return ELAS_OK;
-  size_t need = elas::fwd_workspace_bytes(T, d, d_ff, r, a.dense, a.ab);
-  if (need > kScratchBytes) {
-    a.lean = true;
-    need = elas::fwd_workspace_bytes(T, d, d_ff, r, a.dense, a.ab, true);
-  }
+  const size_t need = fwd_need(a, kScratchBytes);
   if (need > kScratchBytes)
     return fail(ELAS_ERR_WORKSPACE, "this forward needs %zu bytes of workspace; the static scratch holds %zu",
                 need, kScratchBytes);

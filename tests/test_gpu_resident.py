@@ -2,6 +2,8 @@
 around 128, 2048 and 4096 (where the products to the model width change kernel), d
 and d_ff that are not multiples of 64, each rank, each activation mode, against
 the oracle with the gates of the other parity tests."""
+import ctypes
+
 import pytest
 import torch
 
@@ -70,3 +72,32 @@ def test_layout_launch_only_where_it_pays(T, d, F, r, mode, copies):
     finally:
         elas.elas_timing_enable(False)
     assert launches.get("weight_transpose", (0, 0.0))[0] == copies
+
+
+@pytest.mark.parametrize("mode", [0, elas.ELAS_MODE_DENSE])
+def test_factors_ab_need_no_workspace(mode):
+    """Factors as a linear layer stores them are the tiled kernels' operands: a
+    call without a workspace runs those, with the same results; and a workspace
+    short of what even they need is refused."""
+    T, d, F, r, flags = 4479, 520, 5464, 512, elas.ELAS_FACTORS_AB | mode
+    need = elas.elas_lowrank_ffn_fwd_workspace_bytes(T, d, F, r, flags)
+    assert need > 0
+    t = {k: dev_bf16(v) for k, v in ffn_inputs(T, d, F, r, seed_base=8).items()}
+    w = [t[k].t().contiguous() for k in ("U_up", "V_up", "U_down", "V_down")]
+    a = elas.elas_lowrank_ffn_fwd(t["x"], *w, flags=flags)
+    b = {k: None if v is None else torch.full_like(v, 7) for k, v in a.items()}
+
+    def ptr(v):
+        return ctypes.c_void_p(None if v is None else v.data_ptr())
+
+    args = [ptr(v) for v in (t["x"], *w)]
+    out = [ptr(b[k]) for k in ("y", "P", "s_vals", "s_meta", "Z")]
+    torch.cuda.synchronize()
+    assert elas.lib().elas_lowrank_ffn_fwd(*args, T, d, F, r, flags, *out, None, 0, None) == 0
+    torch.cuda.synchronize()
+    for k in a:
+        assert a[k] is None or torch.equal(a[k], b[k]), k
+    flags = mode   # the other orientation always needs its copies
+    need = elas.elas_lowrank_ffn_fwd_workspace_bytes(T, d, F, r, flags)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+    assert elas.lib().elas_lowrank_ffn_fwd(*args, T, d, F, r, flags, *out, ptr(ws), d * r * 2, None) == 4
