@@ -15,9 +15,9 @@ oracle (bf16 inputs, fp32 accumulation).
 * Inputs for which every binary32 sum of the block is exact (checked from
   the oracle's intermediates): every output, including the four fp32 weight
   gradients, matches the oracle bit for bit.
-* Small token counts at the 1B shape exercise the split-K and 128 x 128 tile
-  paths in every activation mode; T = 4096 at the 1B shape runs stream-K and
-  split-K weight gradients over every token.
+* Small token counts at the 1B shape exercise the wave-split kernel (256, 512)
+  and the split-K 128 x 128 tiles (1100, 3000) in every activation mode; T = 4096
+  at the 1B shape runs the weight gradients over every token.
 * Full-size workloads run in the benchmarked configuration: the 1B shape is
   checked on every token and group; the others on sampled tokens (every
   output row depends only on its own token, and the weight gradients are
@@ -208,9 +208,8 @@ def test_exact_fused_epilogue():
 
 def test_exact_1b_shape_every_token():
     """The 1B shape at T = 4096 with sparse +-1 inputs whose every sum is exact
-    in binary32: the K = T weight-gradient products run stream-K (b4, b6)
-    and split-K (b2, b7) over every token, and every output, including the
-    four fp32 weight gradients, must match the oracle bit for bit."""
+    in binary32: every output, including the four fp32 weight gradients (sums
+    over every token), must match the oracle bit for bit."""
     T, d, F, r = 4096, 2048, 5464, 512
     bits = sparse_sign_inputs(T, d, F, r, [1 / 16, 1 / 16, 1 / 64, 1 / 8, 1 / 8, 1 / 4], [0, 0, 0, -8, -4, 0], 51)
     bits["V_up"][:, 5461:] = 0
@@ -347,11 +346,12 @@ def test_zero_tokens():
 
 
 @pytest.mark.parametrize("mode", ["sparse", "dense", "ste"])
-@pytest.mark.parametrize("T", [256, 512])
+@pytest.mark.parametrize("T", [256, 512, 1100, 3000])
 def test_small_token_counts_1b_shape(mode, T):
-    """The 1B shape at token counts where the long-K products split K over the
-    CUs (fp32 partials reduced to bf16) and the K = T products use 128 x 128
-    tiles: parity with the oracle in each activation mode."""
+    """The 1B shape at token counts where the long-K products split K over waves
+    (256, 512) or over the CUs (fp32 partials reduced to bf16; 1100, 3000) and
+    the K = T products use 128 x 128 tiles: parity with the oracle in each
+    activation mode."""
     bits = config_inputs("llama1b", T=T, seed_base=60 + T)
     f, b = offn.run(bits, sparse=(mode != "dense"), ste=(mode == "ste"))
     compare(run_gpu(bits, mode=mode), f, b, bits, mode=mode)

@@ -33,8 +33,8 @@ def _both(bits, flags):
 
 @pytest.mark.parametrize("flags", [0, 2, 16])
 def test_noalloc_matches_workspace_forward_twice(flags):
-    # first call: the 1B shape at 4096 tokens (about 15 MB of transposed factors in the scratch);
-    # second call, smaller: 512 tokens of the 60M shape (small-T split-K partials in the scratch)
+    # first call: the 1B shape at 4096 tokens (about 15 MB of transposed factors in the scratch,
+    # and split-K partials); second call, smaller: 512 tokens of the 60M shape
     if flags == 16:   # the fused forward needs d <= 1024
         first, second = config_inputs("llama350m", T=4096), config_inputs("llama60m", T=512)
     else:
@@ -44,11 +44,14 @@ def test_noalloc_matches_workspace_forward_twice(flags):
 
 
 def test_noalloc_small_token_counts_1b():
-    """At 256 tokens the 1B forward splits K over the CUs: its fp32 partials
-    live in the scratch too (the largest forward workspace, about 31 MB)."""
-    need = elas.elas_lowrank_ffn_fwd_workspace_bytes(256, 2048, 5464, 512, 0)
-    assert need <= elas.elas_noalloc_scratch_bytes()
-    _both(config_inputs("llama1b", T=256), 0)
+    """At 1100 and 3000 tokens the 1B forward splits K over the CUs: its fp32
+    partials live in the scratch too (the largest forward workspace, about
+    31 MB); at 256 it splits K over waves."""
+    for T in (256, 1100, 3000):
+        need = elas.elas_lowrank_ffn_fwd_workspace_bytes(T, 2048, 5464, 512, 0)
+        assert need <= elas.elas_noalloc_scratch_bytes()
+        for flags in (0, elas.ELAS_MODE_DENSE):
+            _both(config_inputs("llama1b", T=T), flags)
     _both(ffn_inputs(77, 64, 136, 24, seed_base=3), 0)
 
 
