@@ -52,9 +52,9 @@ __device__ __forceinline__ int64_t job_pos(const TransposeJob& jb, int64_t row, 
   if (jb.kp > 0) return frag_index(row, col, jb.kp);
   return jb.nsk > 0 ? blocked_index(row, col, jb.nsk) : row * jb.ldo + col;
 }
-// Up to four transposes in one launch (the weight factors of one call): the
-// flat tile index selects the job, so small factors share the launch.
-constexpr int kMaxTransposeJobs = 5;
+// Up to four jobs in one launch (the weight factors of one call): the flat tile
+// index selects the job, so small factors share the launch.
+constexpr int kMaxTransposeJobs = 4;
 struct TransposeBatch {
   TransposeJob job[kMaxTransposeJobs];
   int n;
@@ -170,14 +170,14 @@ hipError_t fill_zero(float* p, int64_t n, hipStream_t st) {
 // waves (two per SIMD) hide LDS and global latency better than four larger
 // wave tiles.
 // Dense products with both operands K-contiguous: 256 x BN tiles, 4 x 2 waves.
-template <int BN, int EPI, bool M_FAST, int DEEP = 0>
-using CfgNT = GemmCfg<256, BN, 4, 2, OP_K, OP_K, EPI, M_FAST, 2, true, false, 128, DEEP>;
+template <int BN, int EPI, bool M_FAST, bool DEEP = false>
+using CfgNT = GemmCfg<256, BN, 4, 2, OP_K, OP_K, EPI, M_FAST, 2, 128, DEEP>;
 // 2:4 sparse A (smfmac) times K-contiguous B: 256 x 256 tiles, 4 x 2 waves
 // (64 x 128 per wave), 64 dense K per step in three LDS stages (150 KB).  The
 // full-width N tile halves the re-reads of the compressed operand, which
 // streams from HBM, and the third stage covers more of its latency.
 // (Measured: 22% faster than 256 x 128 tiles with 128-K steps in two stages.)
-using CfgSP = GemmCfg<256, 256, 4, 2, OP_SP, OP_K, EPI_BF16, false, 3, true, false, 64>;
+using CfgSP = GemmCfg<256, 256, 4, 2, OP_SP, OP_K, EPI_BF16, false, 3, 64>;
 // Compute units of the current device (cached per device id).
 // (Relaxed atomics: concurrent first calls store the same value.)
 int device_cus() {
@@ -242,11 +242,11 @@ hipError_t launch_plain(const char* tag, GemmArgs g, int splits, hipStream_t st)
 // CUs without a tile, 128 x 128 tiles (4 waves of 64 x 64) give four times as
 // many (twice as many for the staged 2:4 epilogues, which need 256 features).
 // In between: 256 x 128 tiles on 8 waves (64 x 64 per wave), four stages (136 KB).
-using CfgSPn = GemmCfg<256, 128, 4, 2, OP_SP, OP_K, EPI_BF16, false, 4, true, false, 64>;
+using CfgSPn = GemmCfg<256, 128, 4, 2, OP_SP, OP_K, EPI_BF16, false, 4, 64>;
 // Row-layout operands (elas_spmm_24): 128 K per step in two stages (136 KB), so that a
 // row's kept values come 128 bytes at a time, a cache line, and not 64.
-using CfgSPr = GemmCfg<256, 128, 4, 2, OP_SP, OP_K, EPI_BF16, false, 2, true, false, 128>;
-using CfgSPs = GemmCfg<128, 128, 2, 2, OP_SP, OP_K, EPI_BF16, false, 3, true, false, 64>;
+using CfgSPr = GemmCfg<256, 128, 4, 2, OP_SP, OP_K, EPI_BF16, false, 2, 128>;
+using CfgSPs = GemmCfg<128, 128, 2, 2, OP_SP, OP_K, EPI_BF16, false, 3, 64>;
 
 bool few_tiles(int64_t M, int64_t N, int bm, int bn) { return cdiv(M, bm) * cdiv(N, bn) * 4 < 3LL * device_cus(); }
 
@@ -273,7 +273,7 @@ size_t small_split_bytes(int64_t M, int64_t N, int64_t K, int bk) {
 }
 template <int EPI, bool M_FAST>
 using CfgNTs = GemmCfg<128, 128, 2, 2, OP_K, OP_K, EPI, M_FAST>;
-using CfgSPsf = GemmCfg<128, 128, 2, 2, OP_SP, OP_K, EPI_F32, false, 3, true, false, 64>;
+using CfgSPsf = GemmCfg<128, 128, 2, 2, OP_SP, OP_K, EPI_F32, false, 3, 64>;
 
 hipError_t reduce_bf16(const float* part, int splits, int64_t M, int64_t N, uint16_t* out, int64_t ldo,
                        hipStream_t st) {
@@ -325,10 +325,11 @@ hipError_t launch_staged(const char* tag, GemmArgs g, hipStream_t st) {
 template <int EPI>
 hipError_t launch_act(const char* tag, const GemmArgs& g, hipStream_t st) {
   if (few_tiles(g.M, g.N, 256, 256)) return launch<CfgNTs<EPI, true>>(tag, g, 1, st);
-  return launch<CfgNT<256, EPI, true, 2>>(tag, g, 1, st);
+  return launch<CfgNT<256, EPI, true, true>>(tag, g, 1, st);
 }
 
-// Token-resident products (resident.h), for the ranks its LDS block is built for.
+// Token-resident products (resident.h), for the ranks it is compiled for: those of the
+// model shapes (its LDS block and registers would hold any multiple of 64 up to 512).
 bool resident_rank(int64_t r) { return r == 128 || r == 256 || r == 512; }
 // The d_ff-wide ones (up projection and dH) are faster than the tiled kernel at
 // every token count (microseconds, tiled against this: 60M at 512 tokens k2

@@ -100,12 +100,6 @@ struct GemmArgs {
   int64_t tok;
 };
 
-// Tiled layout of a compressed 2:4 tensor with tok rows (tokens) and row pitch
-// ld (values, or metadata bytes): rows in blocks of 256 (the last block holds
-// the R < 256 remaining rows) and each row's entries in blocks of BW (32
-// values or 8 metadata bytes: 64 features); block (row block, entry block)
-// holds its R rows x BW entries row-major and contiguously, blocks ordered by
-// row block, then entry block.  Index of entry j of row t:
 // Blocked layout of a K-contiguous [N x K] operand: 256-row panels, each cut
 // into 64-wide K blocks stored contiguously ([256 x 64] row-major, 32 KB),
 // blocks ordered by panel, then K block; nsk = K blocks per panel (K padded
@@ -115,6 +109,12 @@ __host__ __device__ inline int64_t blocked_index(int64_t n, int64_t k, int64_t n
   return (((n >> 8) * nsk + (k >> 6)) << 14) + ((n & 255) << 6) + (k & 63);
 }
 
+// Tiled layout of a compressed 2:4 tensor with tok rows (tokens) and row pitch
+// ld (values, or metadata bytes): rows in blocks of 256 (the last block holds
+// the R < 256 remaining rows) and each row's entries in blocks of BW (32
+// values or 8 metadata bytes: 64 features); block (row block, entry block)
+// holds its R rows x BW entries row-major and contiguously, blocks ordered by
+// row block, then entry block.  Index of entry j of row t:
 template <int BW>
 __device__ __forceinline__ int64_t tiled_index(int64_t t, int64_t j, int64_t tok, int64_t ld) {
   const int64_t tb = t >> 8;
@@ -131,18 +131,12 @@ __device__ __forceinline__ int64_t tiled_step(int64_t row0, int64_t k0, int64_t 
 }
 
 template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, int AMODE_, int BMODE_, int EPI_, bool M_FAST_,
-          int STAGES_ = 2, bool PIPE_ = true, bool PIN_ = false, int SPK_ = 128, int DEEP_ = 0>
+          int STAGES_ = 2, int SPK_ = 128, bool DEEP_ = false>
 struct GemmCfg {
-  // DEEP: separate LDS rings with three stages (prefetched two steps ahead)
-  // for one operand, 1 = A or 2 = B, the one streaming from HBM, and two
-  // (one step ahead) for the other.  Plain-output epilogues only.
-  static constexpr int DEEP = DEEP_;
-  // PIPE: double-buffer the MFMA fragments (read sub-step kk+1 during kk's
-  // MFMAs); off saves registers.
-  static constexpr bool PIPE = PIPE_;
-  // PIN: fence the scheduler around each sub-step's MFMAs, so that the reads
-  // of the next sub-step are issued ahead of them as written (costs registers).
-  static constexpr bool PIN = PIN_;
+  // DEEP: separate LDS rings, with three stages (prefetched two steps ahead)
+  // for B, which streams from HBM, and two (one step ahead) for A.  The
+  // epilogues that write dense dH only.
+  static constexpr bool DEEP = DEEP_;
   static constexpr int BM = BM_, BN = BN_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
   static constexpr int NW = WAVES_M_ * WAVES_N_, NT = 64 * NW;
   static constexpr int AMODE = AMODE_, BMODE = BMODE_, EPI = EPI_;
@@ -173,15 +167,13 @@ struct GemmCfg {
   // EPI_DH copies the stored S tile by DMA during the tile's last K step (the
   // uniform two-stage ring only): the metadata rows go in as dword DMAs of 256
   // bytes, META_DMA_PER_WAVE per wave, so their area is rounded up to that.
-  static constexpr bool PRE_S = EPI_ == EPI_DH && DEEP_ == 0 && STAGES_ == 2;
+  static constexpr bool PRE_S = EPI_ == EPI_DH && !DEEP_ && STAGES_ == 2;
   static_assert(EPI_ != EPI_DH || PRE_S, "EPI_DH copies its S tile during the last K step");
   static constexpr int META_DMA_PER_WAVE = (BN_ * META_PITCH / 4 + 64 * NW - 1) / (64 * NW);
   static constexpr int META_BYTES = PRE_S ? META_DMA_PER_WAVE * NW * 256 : (BN_ * META_PITCH + 15) / 16 * 16;
   static constexpr int A_PART = A_BYTES + AM_BYTES;   // one stage of A (and its metadata)
-  static constexpr int LDS_BYTES = DEEP_ == 1   ? 3 * A_PART + 2 * B_BYTES
-                                   : DEEP_ == 2 ? 2 * A_PART + 3 * B_BYTES
-                                                : STAGES_ * STAGE + (STAGED_EPI ? META_BYTES : 0);
-  static_assert(DEEP_ == 0 || (STAGES_ == 2 && !STAGED_EPI), "three-stage ring: plain epilogues, direct staging");
+  static constexpr int LDS_BYTES = DEEP_ ? 2 * A_PART + 3 * B_BYTES : STAGES_ * STAGE + (STAGED_EPI ? META_BYTES : 0);
+  static_assert(!DEEP_ || (STAGES_ == 2 && !STAGED_EPI), "three-stage ring: plain epilogues");
   static_assert(!STAGED_EPI || (BM_ == 256 && BN_ * BM_ <= STAGE), "staged epilogue layout");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS");
   // a blocked B (GemmArgs::b_nsk) needs 128-byte LDS rows of B (64 K per
@@ -280,12 +272,6 @@ __device__ __forceinline__ void dma_b32_s(const void* sbase, uint32_t voff, uint
 }
 // Non-temporal forms (nt: streamed data that is read once and should not
 // displace what a workgroup keeps in L2).
-__device__ __forceinline__ void dma_b128_nt(const void* g, uint32_t lds_wave_base) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(g), "s"(lds_wave_base) : "memory", "m0");
-}
-__device__ __forceinline__ void dma_b32_nt(const void* g, uint32_t lds_wave_base) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off nt" ::"v"(g), "s"(lds_wave_base) : "memory", "m0");
-}
 __device__ __forceinline__ void dma_b128_nt_s(const void* sbase, uint32_t voff, uint32_t lds_wave_base) {
   asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(uniform_ptr(sbase)),
                "s"(__builtin_amdgcn_readfirstlane(lds_wave_base))
@@ -515,25 +501,17 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
           bfr[slot][j] = *(const bf16x8*)(lB + row * 128 + swz(row, 2 * kk + lhalf) * 16);
         }
       };
-      if constexpr (Cfg::PIPE) read(0, 0);
+      read(0, 0);
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {       // four k16 MFMA steps per 64-wide K step
-        const int cur = Cfg::PIPE ? (kk & 1) : 0;
-        if constexpr (Cfg::PIPE) {
-          if (kk + 1 < 4) read(kk + 1, cur ^ 1);
-        } else {
-          read(kk, 0);
-        }
+        const int cur = kk & 1;
+        if (kk + 1 < 4) read(kk + 1, cur ^ 1);
         hook(kk);
-        // keep the reads of sub-step kk+1 ahead of this sub-step's MFMAs (the
-        // scheduler would otherwise sink each read next to its consumer)
-        if constexpr (Cfg::PIN) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
           for (int j = 0; j < FN; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[cur][i], bfr[cur][j], acc[i][j], 0, 0, 0);
-        if constexpr (Cfg::PIN) __builtin_amdgcn_sched_barrier(0);
       }
     } else {
       constexpr int KK = Cfg::KK;
@@ -575,13 +553,11 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
         int idx[FM];
 #pragma unroll
         for (int i = 0; i < FM; ++i) idx[i] = (int)(meta[i][kk] >> (16 * lhalf));
-        if constexpr (Cfg::PIN) __builtin_amdgcn_sched_barrier(0);   // reads of kk+1 stay ahead of these MFMAs
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
           for (int j = 0; j < FN; ++j)
             acc[i][j] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(af[cur][i], bfr[cur][j], acc[i][j], idx[i], 0, 0);
-        if constexpr (Cfg::PIN) __builtin_amdgcn_sched_barrier(0);
       }
     }
   };
@@ -1114,25 +1090,15 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
       --cb_n;
     };
 
-    if constexpr (Cfg::DEEP != 0) {
-      // The deep operand's stage of global step q is q % 3, the other's q % 2;
-      // A's ring comes first.  Step s issues the shallow operand's step s+1,
-      // then the deep one's step s+2.
-      constexpr bool DA = Cfg::DEEP == 1;
-      constexpr int LOADS_DEEP = DA ? LA + LM : LB;
-      constexpr int NA = DA ? 3 : 2;
-      auto a_off = [](int q) { return (uint32_t)((q % NA) * Cfg::A_PART); };
-      auto b_off = [](int q) { return (uint32_t)(NA * Cfg::A_PART + (q % (DA ? 2 : 3)) * Cfg::B_BYTES); };
-      // x: step relative to the current tile's step 0; q = gs + x
-      auto ahead_deep = [&](int x, int q) __attribute__((always_inline)) {
-        if constexpr (DA) ahead_a(x, a_off(q)); else ahead_b(x, b_off(q));
-      };
-      auto ahead_shallow = [&](int x, int q) __attribute__((always_inline)) {
-        if constexpr (DA) ahead_b(x, b_off(q)); else ahead_a(x, a_off(q));
-      };
-      ahead_deep(0, 0);
-      ahead_shallow(0, 0);
-      ahead_deep(1, 1);
+    if constexpr (Cfg::DEEP) {
+      // B's stage of global step q is q % 3, A's q % 2; A's ring comes first.
+      // Step s issues A's step s+1, then B's step s+2.  (x in ahead_a and
+      // ahead_b: step relative to the current tile's step 0; q = gs + x)
+      auto a_off = [](int q) { return (uint32_t)((q % 2) * Cfg::A_PART); };
+      auto b_off = [](int q) { return (uint32_t)(2 * Cfg::A_PART + (q % 3) * Cfg::B_BYTES); };
+      ahead_b(0, b_off(0));
+      ahead_a(0, a_off(0));
+      ahead_b(1, b_off(1));
       for (;;) {
         zero_acc();
         for (int s = 0; s < tsteps; ++s) {
@@ -1147,34 +1113,30 @@ __global__ __launch_bounds__(Cfg::NT) void gemm_kernel(const GemmArgs g) {
               const int s_end = (TWO && s > nsteps ? nsteps : 0) + s_in - 2;
               int r3 = (gs + s) % 3, r2 = (gs + s) & 1;   // (gs + s) mod 3, mod 2
               for (; s < s_end; ++s) {
-                wait_vmcnt<LOADS_DEEP>();
+                wait_vmcnt<LB>();
                 lds_barrier();
                 const int r3n2 = r3 == 0 ? 2 : r3 - 1;   // (gs + s + 2) mod 3
-                const int a_r = DA ? r3 : r2, b_r = DA ? r2 : r3;   // stages of step s
-                // the shallow operand's step s+1 before this step's MFMAs (it
-                // is needed next step), the deep one's step s+2 after them
-                if constexpr (DA) fast_b(NA * Cfg::A_PART + (r2 ^ 1) * Cfg::B_BYTES);
-                else fast_a((r2 ^ 1) * Cfg::A_PART);
-                compute(smem + a_r * Cfg::A_PART, smem + NA * Cfg::A_PART + b_r * Cfg::B_BYTES, [](int) {});
-                if constexpr (DA) fast_a(r3n2 * Cfg::A_PART);
-                else fast_b(NA * Cfg::A_PART + r3n2 * Cfg::B_BYTES);
+                // A's step s+1 before this step's MFMAs (it is needed next
+                // step), B's step s+2 after them
+                fast_a((r2 ^ 1) * Cfg::A_PART);
+                compute(smem + r2 * Cfg::A_PART, smem + 2 * Cfg::A_PART + r3 * Cfg::B_BYTES, [](int) {});
+                fast_b(2 * Cfg::A_PART + r3n2 * Cfg::B_BYTES);
                 r3 = r3 == 2 ? 0 : r3 + 1;
                 r2 ^= 1;
               }
               if (s >= tsteps) break;
             }
           }
-          // Step s needs both operands' step s; the loads issued after the
-          // shallow operand's step s are the deep one's step s+1 (issued with
-          // it at step s-1).  At a tile's first step the previous epilogue's
+          // Step s needs both operands' step s; the loads issued after A's
+          // step s are B's step s+1 (issued with it at step s-1).  At a tile's first step the previous epilogue's
           // stores are outstanding too: wait for all.
           if (s > 0 && exists(s + 1))
-            wait_vmcnt<LOADS_DEEP>();
+            wait_vmcnt<LB>();
           else
             wait_vmcnt<0>();
           lds_barrier();   // every wave's loads of step s landed; step s-1's reads are done
-          ahead_shallow(s + 1, gs + s + 1);
-          ahead_deep(s + 2, gs + s + 2);
+          ahead_a(s + 1, a_off(gs + s + 1));
+          ahead_b(s + 2, b_off(gs + s + 2));
           compute(smem + a_off(gs + s), smem + b_off(gs + s), [](int) {});
           if (TWO && s == nsteps - 1) stash_h();
         }
