@@ -615,7 +615,7 @@ Route fwd_down(int64_t T, int64_t d, int64_t r, bool lean, bool ab, Route up) {
   const Route w = route_down(T, d, r);
   return (lean || (ab && up != RESIDENT)) && w == RESIDENT ? TILED : w;
 }
-// (ab: the caller passes the factors already K-contiguous; no copies)
+// (ab: the caller passes the factors K-contiguous; copied for the token-resident products only)
 FwdWs fwd_ws(char* p, int64_t T, int64_t d, int64_t F, int64_t r, bool dense, bool ab, bool lean) {
   const int64_t Fp = pad64(F);
   const Route up = fwd_up(T, F, r, dense, ab, lean), down = fwd_down(T, d, r, lean, ab, up);

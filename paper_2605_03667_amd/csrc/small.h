@@ -11,6 +11,10 @@
 // weights are read as a K-contiguous [features x K] matrix, so that nothing is
 // laid out first.
 //
+// Measured against the tiled kernels with their reduces (whole calls, us): forward of 1B
+// at 16 tokens 66 -> 25, at 64 68 -> 30, at 512 55 -> 49, of 350M at 2000 57 -> 40; training
+// step of 350M at 1000 tokens 192 -> 96 (with the one launch of the weight gradients).
+//
 // The chunks are those of the tiled kernels' split-K, and within a chunk the sums
 // run in the tiled kernels' order, so that the results are the same bits and a
 // call's outputs do not depend on which of the two computes them.
